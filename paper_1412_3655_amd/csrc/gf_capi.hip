@@ -164,26 +164,33 @@ gf_status check_omega(double omega, int mode)
     return GF_OK;
 }
 
+const OrOmega& or_omega(gf_lattice L, double omega)
+{
+    if (L->om.omega != omega) L->om = make_or_omega(omega);
+    return L->om;
+}
+
 gf_status do_half_sweep(gf_lattice L, int parity, double omega, int mode)
 {
+    const OrOmega& om = or_omega(L, omega);
     if (L->group == 2) {
         if (is_fp32(L))
-            GF_HIP(gf::launch_su2_or(su2_32(L), L->geom, parity, (float)omega, mode, L->cfg32, L->stream, L->gauge,
+            GF_HIP(gf::launch_su2_or(su2_32(L), L->geom, parity, om, mode, L->cfg32, L->stream, L->gauge,
                                      nullptr));
         else
-            GF_HIP(gf::launch_su2_or(su2_64(L), L->geom, parity, omega, mode, L->cfg64, L->stream, L->gauge, nullptr));
+            GF_HIP(gf::launch_su2_or(su2_64(L), L->geom, parity, om, mode, L->cfg64, L->stream, L->gauge, nullptr));
         return GF_OK;
     }
     if (min8_64(L))
-        GF_HIP(gf::launch_or_half_sweep(field8(L), L->geom, parity, omega, mode, L->cfg64, L->stream, L->gauge));
+        GF_HIP(gf::launch_or_half_sweep(field8(L), L->geom, parity, om, mode, L->cfg64, L->stream, L->gauge));
     else if (is_fp32(L) && L->min8)
-        GF_HIP(gf::launch_or_half_sweep(field8f(L), L->geom, parity, (float)omega, mode, L->cfg32, g_tracking(L),
+        GF_HIP(gf::launch_or_half_sweep(field8f(L), L->geom, parity, om, mode, L->cfg32, g_tracking(L),
                                         L->stream, L->gauge));
     else if (is_fp32(L))
-        GF_HIP(gf::launch_or_half_sweep(field32(L), L->geom, parity, (float)omega, mode, L->cfg32, g_tracking(L),
+        GF_HIP(gf::launch_or_half_sweep(field32(L), L->geom, parity, om, mode, L->cfg32, g_tracking(L),
                                         L->stream, L->gauge));
     else
-        GF_HIP(gf::launch_or_half_sweep(field64(L), L->geom, parity, omega, mode, L->cfg64, L->stream, L->gauge));
+        GF_HIP(gf::launch_or_half_sweep(field64(L), L->geom, parity, om, mode, L->cfg64, L->stream, L->gauge));
     return GF_OK;
 }
 
@@ -349,6 +356,7 @@ gf_status do_measure(gf_lattice L, double* theta, double* F)
 gf_status do_est_sweep(gf_lattice L, double omega, int mode, double* theta_est)
 {
     const SweepConfig& c = is_fp32(L) ? L->cfg32 : L->cfg64;
+    const OrOmega& om = or_omega(L, omega);
     const bool su2 = L->group == 2;
     const uint32_t nb = su2 ? gf::su2_sweep_blocks(L->geom, c) : gf::sweep_blocks(L->geom, c);
     const size_t need = 4 * (size_t)nb;
@@ -363,21 +371,21 @@ gf_status do_est_sweep(gf_lattice L, double omega, int mode, double* theta_est)
     }
     for (int parity = 0; parity < 2; ++parity) {
         if (su2 && is_fp32(L))
-            GF_HIP(gf::launch_su2_or(su2_32(L), L->geom, parity, (float)omega, mode, L->cfg32, L->stream, L->gauge,
+            GF_HIP(gf::launch_su2_or(su2_32(L), L->geom, parity, om, mode, L->cfg32, L->stream, L->gauge,
                                      L->est));
         else if (su2)
-            GF_HIP(gf::launch_su2_or(su2_64(L), L->geom, parity, omega, mode, L->cfg64, L->stream, L->gauge, L->est));
+            GF_HIP(gf::launch_su2_or(su2_64(L), L->geom, parity, om, mode, L->cfg64, L->stream, L->gauge, L->est));
         else if (min8_64(L))
-            GF_HIP(gf::launch_or_half_sweep(field8(L), L->geom, parity, omega, mode, L->cfg64, L->stream, L->gauge,
+            GF_HIP(gf::launch_or_half_sweep(field8(L), L->geom, parity, om, mode, L->cfg64, L->stream, L->gauge,
                                             L->est));
         else if (is_fp32(L) && L->min8)
-            GF_HIP(gf::launch_or_half_sweep(field8f(L), L->geom, parity, (float)omega, mode, L->cfg32, g_tracking(L),
+            GF_HIP(gf::launch_or_half_sweep(field8f(L), L->geom, parity, om, mode, L->cfg32, g_tracking(L),
                                             L->stream, L->gauge, L->est));
         else if (is_fp32(L))
-            GF_HIP(gf::launch_or_half_sweep(field32(L), L->geom, parity, (float)omega, mode, L->cfg32, g_tracking(L),
+            GF_HIP(gf::launch_or_half_sweep(field32(L), L->geom, parity, om, mode, L->cfg32, g_tracking(L),
                                             L->stream, L->gauge, L->est));
         else
-            GF_HIP(gf::launch_or_half_sweep(field64(L), L->geom, parity, omega, mode, L->cfg64, L->stream, L->gauge,
+            GF_HIP(gf::launch_or_half_sweep(field64(L), L->geom, parity, om, mode, L->cfg64, L->stream, L->gauge,
                                             L->est));
     }
     const double V = 2.0 * (double)L->geom.vh;

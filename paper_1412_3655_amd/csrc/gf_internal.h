@@ -40,6 +40,7 @@ struct gf_lattice_ {
     int64_t n_measures = 0, n_estimates = 0;  // exact measurements / fused estimates taken
     bool has_links = false;
     uint32_t anneal_sweeps = 0;             // heat-bath sweep counter (Philox counter word)
+    gf::OrOmega om{};          // the omega of the last overrelaxation sweeps with its power (or_omega)
     gf::SweepConfig cfg64;     // overrelaxation sweeps
     gf::SweepConfig cfg32;
     gf::SweepConfig cfg_hb64;  // heat-bath sweeps (gf_anneal)
@@ -102,6 +103,9 @@ inline bool min8_64(const gf_lattice_* L)
 GField g_tracking(const gf_lattice_* L);
 gf_status check_ready(gf_lattice L);
 gf_status check_omega(double omega, int mode);
+// The lattice's OrOmega, made anew when omega is not that of its last sweeps (a
+// few microseconds, once per call of an entry point).
+const OrOmega& or_omega(gf_lattice L, double omega);
 gf_status do_half_sweep(gf_lattice L, int parity, double omega, int mode);
 gf_status do_sweeps(gf_lattice L, int32_t n, double omega, int mode);
 gf_status do_reunitarize(gf_lattice L);

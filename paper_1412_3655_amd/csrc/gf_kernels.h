@@ -34,11 +34,11 @@ constexpr int GAUGE_COULOMB = 1;
 // nullptr: the launch also writes its per-block sums of tr[Delta Delta^dag]
 // before the update as pairs at est + 2 * parity * sweep_blocks(g, cfg)
 // (colour 0 first, then colour 1: 4 * sweep_blocks doubles for a sweep).
-hipError_t launch_or_half_sweep(const LinkField<double>& f, const Geom& g, int parity, double omega, int mode,
+hipError_t launch_or_half_sweep(const LinkField<double>& f, const Geom& g, int parity, const OrOmega& om, int mode,
                                 const SweepConfig& cfg, hipStream_t st, int gauge = GAUGE_LANDAU,
                                 double* est = nullptr);
 // float32; with gacc.base != nullptr the sweep also accumulates g(x) <- G g(x).
-hipError_t launch_or_half_sweep(const LinkField<float>& f, const Geom& g, int parity, float omega, int mode,
+hipError_t launch_or_half_sweep(const LinkField<float>& f, const Geom& g, int parity, const OrOmega& om, int mode,
                                 const SweepConfig& cfg, const GField& gacc, hipStream_t st,
                                 int gauge = GAUGE_LANDAU, double* est = nullptr);
 uint32_t sweep_blocks(const Geom& g, const SweepConfig& cfg);
@@ -52,19 +52,19 @@ hipError_t launch_hb_half_sweep(const LinkField<float>& f, const Geom& g, int pa
                                 int gauge = GAUGE_LANDAU);
 
 // The Coulomb instantiations (gf_sweep_coulomb.hip) behind gauge = GAUGE_COULOMB.
-hipError_t launch_or_half_sweep_coulomb(const LinkField<double>& f, const Geom& g, int parity, double omega,
+hipError_t launch_or_half_sweep_coulomb(const LinkField<double>& f, const Geom& g, int parity, const OrOmega& om,
                                         int mode, const SweepConfig& cfg, hipStream_t st, double* est);
-hipError_t launch_or_half_sweep_coulomb(const LinkField<float>& f, const Geom& g, int parity, float omega,
+hipError_t launch_or_half_sweep_coulomb(const LinkField<float>& f, const Geom& g, int parity, const OrOmega& om,
                                         int mode, const SweepConfig& cfg, const GField& gacc, hipStream_t st,
                                         double* est);
 // The estimating overrelaxation sweeps (gf_sweep_est.hip, gf_sweep_coulomb_est.hip); est != nullptr.
-hipError_t launch_or_half_sweep_est(const LinkField<double>& f, const Geom& g, int parity, double omega, int mode,
+hipError_t launch_or_half_sweep_est(const LinkField<double>& f, const Geom& g, int parity, const OrOmega& om, int mode,
                                     const SweepConfig& cfg, hipStream_t st, double* est);
-hipError_t launch_or_half_sweep_est(const LinkField<float>& f, const Geom& g, int parity, float omega, int mode,
+hipError_t launch_or_half_sweep_est(const LinkField<float>& f, const Geom& g, int parity, const OrOmega& om, int mode,
                                     const SweepConfig& cfg, const GField& gacc, hipStream_t st, double* est);
-hipError_t launch_or_half_sweep_coulomb_est(const LinkField<double>& f, const Geom& g, int parity, double omega,
+hipError_t launch_or_half_sweep_coulomb_est(const LinkField<double>& f, const Geom& g, int parity, const OrOmega& om,
                                             int mode, const SweepConfig& cfg, hipStream_t st, double* est);
-hipError_t launch_or_half_sweep_coulomb_est(const LinkField<float>& f, const Geom& g, int parity, float omega,
+hipError_t launch_or_half_sweep_coulomb_est(const LinkField<float>& f, const Geom& g, int parity, const OrOmega& om,
                                             int mode, const SweepConfig& cfg, const GField& gacc, hipStream_t st,
                                             double* est);
 hipError_t launch_hb_half_sweep_coulomb(const LinkField<double>& f, const Geom& g, int parity, double T,
@@ -75,28 +75,28 @@ hipError_t launch_hb_half_sweep_coulomb(const LinkField<float>& f, const Geom& g
 
 // Float64 links stored in 8 reals (gf_min8.h): the same sweeps, decoding on
 // load and encoding on store; est as above.
-hipError_t launch_or_half_sweep(const Link8Field& f, const Geom& g, int parity, double omega, int mode,
+hipError_t launch_or_half_sweep(const Link8Field& f, const Geom& g, int parity, const OrOmega& om, int mode,
                                 const SweepConfig& cfg, hipStream_t st, int gauge = GAUGE_LANDAU,
                                 double* est = nullptr);
 hipError_t launch_hb_half_sweep(const Link8Field& f, const Geom& g, int parity, double T, uint64_t seed,
                                 uint32_t sweep, const SweepConfig& cfg, hipStream_t st, int gauge = GAUGE_LANDAU);
-hipError_t launch_or_half_sweep_min8_coulomb(const Link8Field& f, const Geom& g, int parity, double omega, int mode,
+hipError_t launch_or_half_sweep_min8_coulomb(const Link8Field& f, const Geom& g, int parity, const OrOmega& om, int mode,
                                              const SweepConfig& cfg, hipStream_t st, double* est);
-hipError_t launch_or_half_sweep_min8_est(const Link8Field& f, const Geom& g, int parity, double omega, int mode,
+hipError_t launch_or_half_sweep_min8_est(const Link8Field& f, const Geom& g, int parity, const OrOmega& om, int mode,
                                          const SweepConfig& cfg, hipStream_t st, double* est, int gauge);
 
 // Float32 links stored in 8 reals (gf_min8.h): the float32 sweeps (g tracked
 // when gacc.base is set), decoding and encoding in float32; est as above.
-hipError_t launch_or_half_sweep(const Link8Field32& f, const Geom& g, int parity, float omega, int mode,
+hipError_t launch_or_half_sweep(const Link8Field32& f, const Geom& g, int parity, const OrOmega& om, int mode,
                                 const SweepConfig& cfg, const GField& gacc, hipStream_t st, int gauge = GAUGE_LANDAU,
                                 double* est = nullptr);
 hipError_t launch_hb_half_sweep(const Link8Field32& f, const Geom& g, int parity, float T, uint64_t seed,
                                 uint32_t sweep, const SweepConfig& cfg, const GField& gacc, hipStream_t st,
                                 int gauge = GAUGE_LANDAU);
-hipError_t launch_or_half_sweep_min8f_coulomb(const Link8Field32& f, const Geom& g, int parity, float omega,
+hipError_t launch_or_half_sweep_min8f_coulomb(const Link8Field32& f, const Geom& g, int parity, const OrOmega& om,
                                               int mode, const SweepConfig& cfg, const GField& gacc, hipStream_t st,
                                               double* est);
-hipError_t launch_or_half_sweep_min8f_est(const Link8Field32& f, const Geom& g, int parity, float omega, int mode,
+hipError_t launch_or_half_sweep_min8f_est(const Link8Field32& f, const Geom& g, int parity, const OrOmega& om, int mode,
                                           const SweepConfig& cfg, const GField& gacc, hipStream_t st, double* est,
                                           int gauge);
 

@@ -1,0 +1,77 @@
+// gf_or_power.hip -- the coefficients of the power g^omega (OrPower in
+// gf_device.h), computed on the host once per omega.
+#include <cmath>
+
+#include "gf_kernels.h"
+
+namespace gf {
+
+namespace {
+
+constexpr long double kPi = 3.14159265358979323846264338327950288L;
+
+// P(y) = (1 - T_omega(1 - y)) / y and Q(y) = U_{omega-1}(1 - y) from their
+// hypergeometric series 2F1(-omega, omega; 1/2; y/2) and omega 2F1(1 - omega,
+// 1 + omega; 3/2; y/2), whose terms fall by y/2 <= 0.15 each.
+void or_series(long double w, long double y, long double* P, long double* Q)
+{
+    long double c = 1.0L, p = 0.0L, d = w, q = w, yk = 1.0L;
+    for (int k = 1; k <= 32; ++k) {
+        c *= ((long double)(k - 1) * (k - 1) - w * w) / ((2 * k - 1) * (long double)k);
+        d *= ((long double)k * k - w * w) / ((2 * k + 1) * (long double)k);
+        p -= c * yk;
+        yk *= y;
+        q += d * yk;
+    }
+    *P = p;
+    *Q = q;
+}
+
+// Monomial coefficients of the interpolant through (x_i, f_i), i < N (f is
+// overwritten by the divided differences).
+template <int N>
+void interpolate(const long double (&x)[N], long double (&f)[N], long double (&m)[N])
+{
+    for (int j = 1; j < N; ++j)
+        for (int i = N - 1; i >= j; --i) f[i] = (f[i] - f[i - 1]) / (x[i] - x[i - j]);
+    for (int k = 0; k < N; ++k) m[k] = 0.0L;
+    for (int i = N - 1; i >= 0; --i) {
+        for (int k = N - 1; k >= 1; --k) m[k] = m[k - 1] - x[i] * m[k];
+        m[0] = f[i] - x[i] * m[0];
+    }
+}
+
+template <typename R>
+void make_power(long double w, OrPower<R>* out)
+{
+    constexpr int N = OrPower<R>::N;
+    const long double top = 1.0L - sqrtl(0.5L);  // y at psi = pi/4
+    long double x[N], fp[N], fq[N], p[N], q[N];
+    for (int i = 0; i < N; ++i) {
+        x[i] = 0.5L * top * (1.0L + cosl(kPi * (2 * i + 1) / (2 * N)));
+        or_series(w, x[i], &fp[i], &fq[i]);
+    }
+    interpolate<N>(x, fp, p);
+    interpolate<N>(x, fq, q);
+    for (int k = 0; k < N; ++k) {
+        out->p[k] = (R)p[k];
+        out->q[k] = (R)q[k];
+    }
+    out->c_mid = (R)cosl(0.5L * kPi * w);
+    out->s_mid = (R)sinl(0.5L * kPi * w);
+    out->c_far = (R)cosl(kPi * w);
+    out->s_far = (R)sinl(kPi * w);
+}
+
+}  // namespace
+
+OrOmega make_or_omega(double omega)
+{
+    OrOmega om{};
+    om.omega = omega;
+    make_power(omega, &om.p64);
+    make_power(omega, &om.p32);
+    return om;
+}
+
+}  // namespace gf

@@ -34,9 +34,9 @@ uint32_t su2_sweep_blocks(const Geom& g, const SweepConfig& c);
 uint32_t su2_partials(const Geom& g);
 
 // One overrelaxation half-sweep (est as for launch_or_half_sweep: 2 pairs per block of each colour).
-hipError_t launch_su2_or(const Su2Field<double>& f, const Geom& g, int parity, double omega, int mode,
+hipError_t launch_su2_or(const Su2Field<double>& f, const Geom& g, int parity, const OrOmega& om, int mode,
                          const SweepConfig& c, hipStream_t st, int gauge, double* est);
-hipError_t launch_su2_or(const Su2Field<float>& f, const Geom& g, int parity, float omega, int mode,
+hipError_t launch_su2_or(const Su2Field<float>& f, const Geom& g, int parity, const OrOmega& om, int mode,
                          const SweepConfig& c, hipStream_t st, int gauge, double* est);
 // One heat-bath half-sweep at temperature T (Philox key seed, sweep counter sweep).
 hipError_t launch_su2_hb(const Su2Field<double>& f, const Geom& g, int parity, double T, uint64_t seed,

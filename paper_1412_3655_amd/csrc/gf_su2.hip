@@ -299,10 +299,10 @@ hipError_t launch_gauge(const Su2Field<R>& f, const Geom& g, int parity, const R
 }
 
 template <typename R>
-hipError_t or_impl(const Su2Field<R>& f, const Geom& g, int parity, R omega, int mode, const SweepConfig& c,
+hipError_t or_impl(const Su2Field<R>& f, const Geom& g, int parity, const OrOmega& om, int mode, const SweepConfig& c,
                    hipStream_t st, int gauge, double* est)
 {
-    const Rule<R> rule{omega, R(1), 0u, 0u, 0u};
+    const Rule<R> rule = or_rule<R>(om);
     return mode == OR_EXACT ? launch_gauge<R, 0>(f, g, parity, rule, c, st, gauge, est)
                             : launch_gauge<R, 1>(f, g, parity, rule, c, st, gauge, est);
 }
@@ -311,7 +311,7 @@ template <typename R>
 hipError_t hb_impl(const Su2Field<R>& f, const Geom& g, int parity, R T, uint64_t seed, uint32_t sweep,
                    const SweepConfig& c, hipStream_t st, int gauge)
 {
-    const Rule<R> rule{R(1), T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep};
+    const Rule<R> rule{R(1), T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep, {}};
     return launch_gauge<R, HEATBATH>(f, g, parity, rule, c, st, gauge, nullptr);
 }
 
@@ -370,15 +370,15 @@ uint32_t su2_sweep_blocks(const Geom& g, const SweepConfig& c)
     return (g.vh + (uint32_t)c.block - 1) / (uint32_t)c.block;
 }
 
-hipError_t launch_su2_or(const Su2Field<double>& f, const Geom& g, int parity, double omega, int mode,
+hipError_t launch_su2_or(const Su2Field<double>& f, const Geom& g, int parity, const OrOmega& om, int mode,
                          const SweepConfig& c, hipStream_t st, int gauge, double* est)
 {
-    return or_impl(f, g, parity, omega, mode, c, st, gauge, est);
+    return or_impl(f, g, parity, om, mode, c, st, gauge, est);
 }
-hipError_t launch_su2_or(const Su2Field<float>& f, const Geom& g, int parity, float omega, int mode,
+hipError_t launch_su2_or(const Su2Field<float>& f, const Geom& g, int parity, const OrOmega& om, int mode,
                          const SweepConfig& c, hipStream_t st, int gauge, double* est)
 {
-    return or_impl(f, g, parity, omega, mode, c, st, gauge, est);
+    return or_impl(f, g, parity, om, mode, c, st, gauge, est);
 }
 hipError_t launch_su2_hb(const Su2Field<double>& f, const Geom& g, int parity, double T, uint64_t seed,
                          uint32_t sweep, const SweepConfig& c, hipStream_t st, int gauge)

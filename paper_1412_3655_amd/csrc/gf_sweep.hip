@@ -17,21 +17,21 @@ bool sweep_config_valid(const SweepConfig& c)
     return tps_ok && blk_ok && nt_ok && minw_ok && !(c.tps == 1 && c.block == 512);
 }
 
-hipError_t launch_or_half_sweep(const LinkField<double>& f, const Geom& g, int parity, double omega, int mode,
+hipError_t launch_or_half_sweep(const LinkField<double>& f, const Geom& g, int parity, const OrOmega& om, int mode,
                                 const SweepConfig& cfg, hipStream_t st, int gauge, double* est)
 {
-    if (gauge == GAUGE_COULOMB) return launch_or_half_sweep_coulomb(f, g, parity, omega, mode, cfg, st, est);
-    if (est) return launch_or_half_sweep_est(f, g, parity, omega, mode, cfg, st, est);
-    return sweep_impl::or_half_sweep<NDIR_LANDAU, false>(f, g, parity, omega, mode, cfg, st, nullptr);
+    if (gauge == GAUGE_COULOMB) return launch_or_half_sweep_coulomb(f, g, parity, om, mode, cfg, st, est);
+    if (est) return launch_or_half_sweep_est(f, g, parity, om, mode, cfg, st, est);
+    return sweep_impl::or_half_sweep<NDIR_LANDAU, false>(f, g, parity, om, mode, cfg, st, nullptr);
 }
 
-hipError_t launch_or_half_sweep(const LinkField<float>& f, const Geom& g, int parity, float omega, int mode,
+hipError_t launch_or_half_sweep(const LinkField<float>& f, const Geom& g, int parity, const OrOmega& om, int mode,
                                 const SweepConfig& cfg, const GField& gacc, hipStream_t st, int gauge, double* est)
 {
     if (gauge == GAUGE_COULOMB)
-        return launch_or_half_sweep_coulomb(f, g, parity, omega, mode, cfg, gacc, st, est);
-    if (est) return launch_or_half_sweep_est(f, g, parity, omega, mode, cfg, gacc, st, est);
-    return sweep_impl::or_half_sweep<NDIR_LANDAU, false>(f, g, parity, omega, mode, cfg, gacc, st, nullptr);
+        return launch_or_half_sweep_coulomb(f, g, parity, om, mode, cfg, gacc, st, est);
+    if (est) return launch_or_half_sweep_est(f, g, parity, om, mode, cfg, gacc, st, est);
+    return sweep_impl::or_half_sweep<NDIR_LANDAU, false>(f, g, parity, om, mode, cfg, gacc, st, nullptr);
 }
 
 uint32_t sweep_blocks(const Geom& g, const SweepConfig& cfg)

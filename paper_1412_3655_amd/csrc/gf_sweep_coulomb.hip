@@ -10,19 +10,19 @@
 
 namespace gf {
 
-hipError_t launch_or_half_sweep_coulomb(const LinkField<double>& f, const Geom& g, int parity, double omega,
+hipError_t launch_or_half_sweep_coulomb(const LinkField<double>& f, const Geom& g, int parity, const OrOmega& om,
                                         int mode, const SweepConfig& cfg, hipStream_t st, double* est)
 {
-    if (est) return launch_or_half_sweep_coulomb_est(f, g, parity, omega, mode, cfg, st, est);
-    return sweep_impl::or_half_sweep<NDIR_COULOMB, false>(f, g, parity, omega, mode, cfg, st, nullptr);
+    if (est) return launch_or_half_sweep_coulomb_est(f, g, parity, om, mode, cfg, st, est);
+    return sweep_impl::or_half_sweep<NDIR_COULOMB, false>(f, g, parity, om, mode, cfg, st, nullptr);
 }
 
-hipError_t launch_or_half_sweep_coulomb(const LinkField<float>& f, const Geom& g, int parity, float omega,
+hipError_t launch_or_half_sweep_coulomb(const LinkField<float>& f, const Geom& g, int parity, const OrOmega& om,
                                         int mode, const SweepConfig& cfg, const GField& gacc, hipStream_t st,
                                         double* est)
 {
-    if (est) return launch_or_half_sweep_coulomb_est(f, g, parity, omega, mode, cfg, gacc, st, est);
-    return sweep_impl::or_half_sweep<NDIR_COULOMB, false>(f, g, parity, omega, mode, cfg, gacc, st, nullptr);
+    if (est) return launch_or_half_sweep_coulomb_est(f, g, parity, om, mode, cfg, gacc, st, est);
+    return sweep_impl::or_half_sweep<NDIR_COULOMB, false>(f, g, parity, om, mode, cfg, gacc, st, nullptr);
 }
 
 hipError_t launch_hb_half_sweep_coulomb(const LinkField<double>& f, const Geom& g, int parity, double T,

@@ -8,16 +8,16 @@
 
 namespace gf {
 
-hipError_t launch_or_half_sweep_coulomb_est(const LinkField<double>& f, const Geom& g, int parity, double omega, int mode,
+hipError_t launch_or_half_sweep_coulomb_est(const LinkField<double>& f, const Geom& g, int parity, const OrOmega& om, int mode,
                                             const SweepConfig& cfg, hipStream_t st, double* est)
 {
-    return sweep_impl::or_half_sweep<NDIR_COULOMB, true>(f, g, parity, omega, mode, cfg, st, est);
+    return sweep_impl::or_half_sweep<NDIR_COULOMB, true>(f, g, parity, om, mode, cfg, st, est);
 }
 
-hipError_t launch_or_half_sweep_coulomb_est(const LinkField<float>& f, const Geom& g, int parity, float omega, int mode,
+hipError_t launch_or_half_sweep_coulomb_est(const LinkField<float>& f, const Geom& g, int parity, const OrOmega& om, int mode,
                                             const SweepConfig& cfg, const GField& gacc, hipStream_t st, double* est)
 {
-    return sweep_impl::or_half_sweep<NDIR_COULOMB, true>(f, g, parity, omega, mode, cfg, gacc, st, est);
+    return sweep_impl::or_half_sweep<NDIR_COULOMB, true>(f, g, parity, om, mode, cfg, gacc, st, est);
 }
 
 }  // namespace gf

@@ -145,20 +145,20 @@ hipError_t launch_mode(const F& f, const Geom& g, int parity, const Rule<R>& rul
 
 // EST = true needs est != nullptr; EST = false ignores est.
 template <int NDIR, bool EST>
-hipError_t or_half_sweep(const LinkField<double>& f, const Geom& g, int parity, double omega, int mode,
+hipError_t or_half_sweep(const LinkField<double>& f, const Geom& g, int parity, const OrOmega& om, int mode,
                          const SweepConfig& cfg, hipStream_t st, double* est)
 {
     const GField none{nullptr, 0};
-    const Rule<double> rule{omega, 1.0, 0u, 0u, 0u};
+    const Rule<double> rule = or_rule<double>(om);
     return mode == OR_EXACT ? launch_mode<NDIR, EST, double, 0, false>(f, g, parity, rule, cfg, none, st, est)
                             : launch_mode<NDIR, EST, double, 1, false>(f, g, parity, rule, cfg, none, st, est);
 }
 
 template <int NDIR, bool EST>
-hipError_t or_half_sweep(const LinkField<float>& f, const Geom& g, int parity, float omega, int mode,
+hipError_t or_half_sweep(const LinkField<float>& f, const Geom& g, int parity, const OrOmega& om, int mode,
                          const SweepConfig& cfg, const GField& gacc, hipStream_t st, double* est)
 {
-    const Rule<float> rule{omega, 1.0f, 0u, 0u, 0u};
+    const Rule<float> rule = or_rule<float>(om);
     if (gacc.base)
         return mode == OR_EXACT ? launch_mode<NDIR, EST, float, 0, true>(f, g, parity, rule, cfg, gacc, st, est)
                                 : launch_mode<NDIR, EST, float, 1, true>(f, g, parity, rule, cfg, gacc, st, est);
@@ -171,7 +171,7 @@ hipError_t hb_half_sweep(const LinkField<double>& f, const Geom& g, int parity, 
                          uint32_t sweep, const SweepConfig& cfg, hipStream_t st)
 {
     const GField none{nullptr, 0};
-    const Rule<double> rule{1.0, T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep};
+    const Rule<double> rule{1.0, T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep, {}};
     return launch_mode<NDIR, false, double, HEATBATH, false>(f, g, parity, rule, cfg, none, st, nullptr);
 }
 
@@ -179,7 +179,7 @@ template <int NDIR>
 hipError_t hb_half_sweep(const LinkField<float>& f, const Geom& g, int parity, float T, uint64_t seed,
                          uint32_t sweep, const SweepConfig& cfg, const GField& gacc, hipStream_t st)
 {
-    const Rule<float> rule{1.0f, T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep};
+    const Rule<float> rule{1.0f, T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep, {}};
     if (gacc.base) return launch_mode<NDIR, false, float, HEATBATH, true>(f, g, parity, rule, cfg, gacc, st, nullptr);
     return launch_mode<NDIR, false, float, HEATBATH, false>(f, g, parity, rule, cfg, gacc, st, nullptr);
 }
@@ -187,11 +187,11 @@ hipError_t hb_half_sweep(const LinkField<float>& f, const Geom& g, int parity, f
 // Float64 links stored in 8 reals (Link8Field): the same kernel, decoding on
 // load and encoding on store.
 template <int NDIR, bool EST>
-hipError_t or_half_sweep(const Link8Field& f, const Geom& g, int parity, double omega, int mode,
+hipError_t or_half_sweep(const Link8Field& f, const Geom& g, int parity, const OrOmega& om, int mode,
                          const SweepConfig& cfg, hipStream_t st, double* est)
 {
     const GField none{nullptr, 0};
-    const Rule<double> rule{omega, 1.0, 0u, 0u, 0u};
+    const Rule<double> rule = or_rule<double>(om);
     return mode == OR_EXACT ? launch_mode<NDIR, EST, double, 0, false>(f, g, parity, rule, cfg, none, st, est)
                             : launch_mode<NDIR, EST, double, 1, false>(f, g, parity, rule, cfg, none, st, est);
 }
@@ -201,17 +201,17 @@ hipError_t hb_half_sweep(const Link8Field& f, const Geom& g, int parity, double 
                          const SweepConfig& cfg, hipStream_t st)
 {
     const GField none{nullptr, 0};
-    const Rule<double> rule{1.0, T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep};
+    const Rule<double> rule{1.0, T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep, {}};
     return launch_mode<NDIR, false, double, HEATBATH, false>(f, g, parity, rule, cfg, none, st, nullptr);
 }
 
 // Float32 links stored in 8 reals (Link8Field32): the float32 sweeps, g(x)
 // tracked when gacc.base is set.
 template <int NDIR, bool EST>
-hipError_t or_half_sweep(const Link8Field32& f, const Geom& g, int parity, float omega, int mode,
+hipError_t or_half_sweep(const Link8Field32& f, const Geom& g, int parity, const OrOmega& om, int mode,
                          const SweepConfig& cfg, const GField& gacc, hipStream_t st, double* est)
 {
-    const Rule<float> rule{omega, 1.0f, 0u, 0u, 0u};
+    const Rule<float> rule = or_rule<float>(om);
     if (gacc.base)
         return mode == OR_EXACT ? launch_mode<NDIR, EST, float, 0, true>(f, g, parity, rule, cfg, gacc, st, est)
                                 : launch_mode<NDIR, EST, float, 1, true>(f, g, parity, rule, cfg, gacc, st, est);
@@ -223,7 +223,7 @@ template <int NDIR>
 hipError_t hb_half_sweep(const Link8Field32& f, const Geom& g, int parity, float T, uint64_t seed, uint32_t sweep,
                          const SweepConfig& cfg, const GField& gacc, hipStream_t st)
 {
-    const Rule<float> rule{1.0f, T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep};
+    const Rule<float> rule{1.0f, T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep, {}};
     if (gacc.base) return launch_mode<NDIR, false, float, HEATBATH, true>(f, g, parity, rule, cfg, gacc, st, nullptr);
     return launch_mode<NDIR, false, float, HEATBATH, false>(f, g, parity, rule, cfg, gacc, st, nullptr);
 }

@@ -10,12 +10,12 @@
 
 namespace gf {
 
-hipError_t launch_or_half_sweep(const Link8Field& f, const Geom& g, int parity, double omega, int mode,
+hipError_t launch_or_half_sweep(const Link8Field& f, const Geom& g, int parity, const OrOmega& om, int mode,
                                 const SweepConfig& cfg, hipStream_t st, int gauge, double* est)
 {
-    if (gauge == GAUGE_COULOMB) return launch_or_half_sweep_min8_coulomb(f, g, parity, omega, mode, cfg, st, est);
-    if (est) return launch_or_half_sweep_min8_est(f, g, parity, omega, mode, cfg, st, est, GAUGE_LANDAU);
-    return sweep_impl::or_half_sweep<NDIR_LANDAU, false>(f, g, parity, omega, mode, cfg, st, nullptr);
+    if (gauge == GAUGE_COULOMB) return launch_or_half_sweep_min8_coulomb(f, g, parity, om, mode, cfg, st, est);
+    if (est) return launch_or_half_sweep_min8_est(f, g, parity, om, mode, cfg, st, est, GAUGE_LANDAU);
+    return sweep_impl::or_half_sweep<NDIR_LANDAU, false>(f, g, parity, om, mode, cfg, st, nullptr);
 }
 
 }  // namespace gf

@@ -5,11 +5,11 @@
 
 namespace gf {
 
-hipError_t launch_or_half_sweep_min8_coulomb(const Link8Field& f, const Geom& g, int parity, double omega, int mode,
+hipError_t launch_or_half_sweep_min8_coulomb(const Link8Field& f, const Geom& g, int parity, const OrOmega& om, int mode,
                                              const SweepConfig& cfg, hipStream_t st, double* est)
 {
-    if (est) return launch_or_half_sweep_min8_est(f, g, parity, omega, mode, cfg, st, est, GAUGE_COULOMB);
-    return sweep_impl::or_half_sweep<NDIR_COULOMB, false>(f, g, parity, omega, mode, cfg, st, nullptr);
+    if (est) return launch_or_half_sweep_min8_est(f, g, parity, om, mode, cfg, st, est, GAUGE_COULOMB);
+    return sweep_impl::or_half_sweep<NDIR_COULOMB, false>(f, g, parity, om, mode, cfg, st, nullptr);
 }
 
 }  // namespace gf

@@ -5,12 +5,12 @@
 
 namespace gf {
 
-hipError_t launch_or_half_sweep_min8_est(const Link8Field& f, const Geom& g, int parity, double omega, int mode,
+hipError_t launch_or_half_sweep_min8_est(const Link8Field& f, const Geom& g, int parity, const OrOmega& om, int mode,
                                          const SweepConfig& cfg, hipStream_t st, double* est, int gauge)
 {
     if (gauge == GAUGE_COULOMB)
-        return sweep_impl::or_half_sweep<NDIR_COULOMB, true>(f, g, parity, omega, mode, cfg, st, est);
-    return sweep_impl::or_half_sweep<NDIR_LANDAU, true>(f, g, parity, omega, mode, cfg, st, est);
+        return sweep_impl::or_half_sweep<NDIR_COULOMB, true>(f, g, parity, om, mode, cfg, st, est);
+    return sweep_impl::or_half_sweep<NDIR_LANDAU, true>(f, g, parity, om, mode, cfg, st, est);
 }
 
 }  // namespace gf

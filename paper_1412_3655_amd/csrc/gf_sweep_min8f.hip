@@ -9,13 +9,13 @@
 
 namespace gf {
 
-hipError_t launch_or_half_sweep(const Link8Field32& f, const Geom& g, int parity, float omega, int mode,
+hipError_t launch_or_half_sweep(const Link8Field32& f, const Geom& g, int parity, const OrOmega& om, int mode,
                                 const SweepConfig& cfg, const GField& gacc, hipStream_t st, int gauge, double* est)
 {
     if (gauge == GAUGE_COULOMB)
-        return launch_or_half_sweep_min8f_coulomb(f, g, parity, omega, mode, cfg, gacc, st, est);
-    if (est) return launch_or_half_sweep_min8f_est(f, g, parity, omega, mode, cfg, gacc, st, est, GAUGE_LANDAU);
-    return sweep_impl::or_half_sweep<NDIR_LANDAU, false>(f, g, parity, omega, mode, cfg, gacc, st, nullptr);
+        return launch_or_half_sweep_min8f_coulomb(f, g, parity, om, mode, cfg, gacc, st, est);
+    if (est) return launch_or_half_sweep_min8f_est(f, g, parity, om, mode, cfg, gacc, st, est, GAUGE_LANDAU);
+    return sweep_impl::or_half_sweep<NDIR_LANDAU, false>(f, g, parity, om, mode, cfg, gacc, st, nullptr);
 }
 
 }  // namespace gf

@@ -5,12 +5,12 @@
 
 namespace gf {
 
-hipError_t launch_or_half_sweep_min8f_coulomb(const Link8Field32& f, const Geom& g, int parity, float omega,
+hipError_t launch_or_half_sweep_min8f_coulomb(const Link8Field32& f, const Geom& g, int parity, const OrOmega& om,
                                               int mode, const SweepConfig& cfg, const GField& gacc, hipStream_t st,
                                               double* est)
 {
-    if (est) return launch_or_half_sweep_min8f_est(f, g, parity, omega, mode, cfg, gacc, st, est, GAUGE_COULOMB);
-    return sweep_impl::or_half_sweep<NDIR_COULOMB, false>(f, g, parity, omega, mode, cfg, gacc, st, nullptr);
+    if (est) return launch_or_half_sweep_min8f_est(f, g, parity, om, mode, cfg, gacc, st, est, GAUGE_COULOMB);
+    return sweep_impl::or_half_sweep<NDIR_COULOMB, false>(f, g, parity, om, mode, cfg, gacc, st, nullptr);
 }
 
 }  // namespace gf

@@ -138,6 +138,7 @@ gf_status tune(gf_lattice L, gf_prec kernel, bool heat_bath, int32_t n_sweeps, c
     const Su2Field<double> q64{(double2*)scratch, L->geom.ld};
     const Link8Field f8{(double2*)scratch, L->geom.ld};
     const Link8Field32 f8f{(float4*)scratch, L->geom.ld};
+    const OrOmega om = make_or_omega(1.7);
     uint32_t hb_sweep = 0;
     // the register cap changes only the one-lane float64 kernel (every other
     // shape already runs 2 or more waves per SIMD)
@@ -166,29 +167,29 @@ gf_status tune(gf_lattice L, gf_prec kernel, bool heat_bath, int32_t n_sweeps, c
                     else if (su2 && heat_bath)
                         r = launch_su2_hb(q64, L->geom, p, 1.0, 1u, hb_sweep, c, L->stream, L->gauge);
                     else if (su2 && kernel == GF_FP32)
-                        r = launch_su2_or(q32, L->geom, p, 1.7f, GF_OR_EXACT, c, L->stream, L->gauge, nullptr);
+                        r = launch_su2_or(q32, L->geom, p, om, GF_OR_EXACT, c, L->stream, L->gauge, nullptr);
                     else if (su2)
-                        r = launch_su2_or(q64, L->geom, p, 1.7, GF_OR_EXACT, c, L->stream, L->gauge, nullptr);
+                        r = launch_su2_or(q64, L->geom, p, om, GF_OR_EXACT, c, L->stream, L->gauge, nullptr);
                     else if (m8 && heat_bath && kernel == GF_FP32)
                         r = launch_hb_half_sweep(f8f, L->geom, p, 1.0f, 1u, hb_sweep, c, track ? g_s : g_none,
                                                  L->stream, L->gauge);
                     else if (m8 && kernel == GF_FP32)
-                        r = launch_or_half_sweep(f8f, L->geom, p, 1.7f, GF_OR_EXACT, c, track ? g_s : g_none,
+                        r = launch_or_half_sweep(f8f, L->geom, p, om, GF_OR_EXACT, c, track ? g_s : g_none,
                                                  L->stream, L->gauge);
                     else if (m8 && heat_bath)
                         r = launch_hb_half_sweep(f8, L->geom, p, 1.0, 1u, hb_sweep, c, L->stream, L->gauge);
                     else if (m8)
-                        r = launch_or_half_sweep(f8, L->geom, p, 1.7, GF_OR_EXACT, c, L->stream, L->gauge);
+                        r = launch_or_half_sweep(f8, L->geom, p, om, GF_OR_EXACT, c, L->stream, L->gauge);
                     else if (heat_bath && kernel == GF_FP32)
                         r = launch_hb_half_sweep(f32, L->geom, p, 1.0f, 1u, hb_sweep, c, track ? g_s : g_none,
                                                  L->stream, L->gauge);
                     else if (heat_bath)
                         r = launch_hb_half_sweep(f64, L->geom, p, 1.0, 1u, hb_sweep, c, L->stream, L->gauge);
                     else if (kernel == GF_FP32)
-                        r = launch_or_half_sweep(f32, L->geom, p, 1.7f, GF_OR_EXACT, c, track ? g_s : g_none,
+                        r = launch_or_half_sweep(f32, L->geom, p, om, GF_OR_EXACT, c, track ? g_s : g_none,
                                                  L->stream, L->gauge);
                     else
-                        r = launch_or_half_sweep(f64, L->geom, p, 1.7, GF_OR_EXACT, c, L->stream, L->gauge);
+                        r = launch_or_half_sweep(f64, L->geom, p, om, GF_OR_EXACT, c, L->stream, L->gauge);
                     if (r != hipSuccess) return r;
                 }
                 ++hb_sweep;
