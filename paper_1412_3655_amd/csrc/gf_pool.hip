@@ -260,8 +260,9 @@ __global__ void __launch_bounds__(PBLOCK) k_pool_reunit(const SlotDev* __restric
     }
 }
 
-// Tile b of a slot = measurement block (parity = b / nb, block = b % nb) of the
-// single-lattice measurement, writing the same partial.
+// Tile b of a slot = measurement block (parity = b & 1, block = b >> 1) of the
+// single-lattice measurement, writing the same partial.  Each XCD takes a
+// contiguous run of the tiles, as there (block b runs on XCD b % 8).
 template <typename R, bool M8>
 __global__ void __launch_bounds__(PBLOCK) k_pool_measure(const SlotDev* __restrict__ slots,
                                                          const Entry* __restrict__ list,
@@ -269,20 +270,21 @@ __global__ void __launch_bounds__(PBLOCK) k_pool_measure(const SlotDev* __restri
 {
     const uint32_t n = *count;
     const uint32_t total = list[n].first;
-    for (uint32_t t = blockIdx.x; t < total; t += gridDim.x) {
+    const uint32_t xcd = blockIdx.x % kXcds, last = xcd_first(xcd + 1u, total);
+    for (uint32_t t = xcd_first(xcd, total) + blockIdx.x / kXcds; t < last; t += gridDim.x / kXcds) {
         const uint32_t i = find_entry(list, n, t);
         const SlotDev sd = slots[list[i].slot];
         const uint32_t b = t - list[i].first;
         const uint32_t nb = (sd.g.vh + PBLOCK - 1) / PBLOCK;
-        const int parity = (int)(b / nb);
-        const uint32_t h = (b % nb) * PBLOCK + threadIdx.x;
+        const int parity = (int)(b & 1u);
+        const uint32_t h = (b >> 1) * PBLOCK + threadIdx.x;
         double th = 0.0, fr = 0.0;
         if constexpr (M8) {
             if (h < sd.g.vh) measure_site(field8_of(sd), sd.g, parity, h, th, fr);
         } else {
             if (h < sd.g.vh) measure_site(field_of<R>(sd), sd.g, parity, h, th, fr);
         }
-        block_sum2<PBLOCK>(th, fr, sd.partial + 2 * (size_t)b);
+        block_sum2<PBLOCK>(th, fr, sd.partial + 2 * ((size_t)parity * nb + (b >> 1)));
         __syncthreads();
     }
 }
@@ -1020,7 +1022,7 @@ gf_status gf_pool_create(const gf_pool_config* cfg, void* hip_stream, gf_pool* o
         return fail(GF_E_HIP, "pool allocation failed: %s", hipGetErrorString(e));
     }
     // persistent grid of the reunitarisation / measurement kernels: a few resident blocks per compute unit
-    P->grid_other = 4 * ncu;
+    P->grid_other = 4 * (ncu + 7) / 8 * 8;  // whole rounds over the XCDs (k_pool_measure)
     P->seg_tiles.assign(nseg, 0);
     std::memset(P->slots_pin, 0, sizeof(SlotDev) * c.max_slots);
     *out = P;

@@ -141,16 +141,18 @@ __global__ void __launch_bounds__(BLOCK) k_su2_half_sweep(Su2Field<R> f, Geom g,
 }
 
 // Landau: per-block (theta, F) partial sums over both colours (blocks alternate colours tile by tile).
-// Coulomb: the same per timeslice t = blockIdx.y.
+// Coulomb: the same per timeslice; nb blocks per timeslice (Landau: all blocks).
 template <typename R, int NDIR>
-__global__ void __launch_bounds__(RB) k_su2_measure(Su2Field<R> f, Geom g, double* partial)
+__global__ void __launch_bounds__(RB) k_su2_measure(Su2Field<R> f, Geom g, uint32_t nb, double* partial)
 {
-    const int parity = (int)(blockIdx.x & 1u);
-    const uint32_t k = (blockIdx.x >> 1) * RB + threadIdx.x;
+    const uint32_t l = xcd_block(blockIdx.x, gridDim.x);
+    const uint32_t t = l / nb, b = l % nb;
+    const int parity = (int)(b & 1u);
+    const uint32_t k = (b >> 1) * RB + threadIdx.x;
     const uint32_t span = NDIR == 4 ? g.vh : g.hs3;
     double th = 0.0, fr = 0.0;
     if (k < span) {
-        const uint32_t h = (NDIR == 4 ? 0u : blockIdx.y * g.hs3) + k;
+        const uint32_t h = (NDIR == 4 ? 0u : t * g.hs3) + k;
         const Site s = decode_site(g, parity, h);
         double c1 = 0.0, c2 = 0.0, c3 = 0.0;
 #pragma unroll
@@ -164,7 +166,7 @@ __global__ void __launch_bounds__(RB) k_su2_measure(Su2Field<R> f, Geom g, doubl
         }
         th = 2.0 * (c1 * c1 + c2 * c2 + c3 * c3);
     }
-    block_sum2<RB>(th, fr, partial + 2 * ((size_t)blockIdx.y * gridDim.x + blockIdx.x));
+    block_sum2<RB>(th, fr, partial + 2 * (size_t)l);
 }
 
 __global__ void __launch_bounds__(RB) k_su2_finalize(const double* partial, uint32_t n, double s0, double s1,
@@ -176,8 +178,10 @@ __global__ void __launch_bounds__(RB) k_su2_finalize(const double* partial, uint
 template <typename R>
 __global__ void __launch_bounds__(RB) k_su2_plaquette(Su2Field<R> f, Geom g, double* partial)
 {
-    const int parity = blockIdx.y;
-    const uint32_t h = blockIdx.x * RB + threadIdx.x;
+    const uint32_t l = xcd_block(blockIdx.x, gridDim.x);
+    const int parity = (int)(l & 1u);
+    const uint32_t tile = l >> 1, tiles = gridDim.x >> 1;
+    const uint32_t h = tile * RB + threadIdx.x;
     double acc = 0.0;
     if (h < g.vh) {
         const Site s = decode_site(g, parity, h);
@@ -197,7 +201,7 @@ __global__ void __launch_bounds__(RB) k_su2_plaquette(Su2Field<R> f, Geom g, dou
                 acc += 2.0 * qmul(qmul(A, B), qdag(qmul(D, C))).b0;
             }
     }
-    block_sum2<RB>(acc, 0.0, partial + 2 * (size_t)(blockIdx.y * gridDim.x + blockIdx.x));
+    block_sum2<RB>(acc, 0.0, partial + 2 * (size_t)(parity * tiles + tile));
 }
 
 template <typename R>
@@ -325,14 +329,14 @@ hipError_t measure_impl(const Su2Field<R>& f, const Geom& g, int gauge, double* 
 {
     if (gauge == GAUGE_COULOMB) {
         const uint32_t nb = 2 * ((g.hs3 + RB - 1) / RB);
-        hipLaunchKernelGGL((k_su2_measure<R, NDIR_COULOMB>), dim3(nb, (uint32_t)g.n[3]), dim3(RB), 0, st, f, g,
-                           partial);
+        hipLaunchKernelGGL((k_su2_measure<R, NDIR_COULOMB>), dim3(nb * (uint32_t)g.n[3]), dim3(RB), 0, st, f, g,
+                           nb, partial);
         const double V3 = 2.0 * (double)g.hs3;
         hipLaunchKernelGGL(k_su2_finalize, dim3((uint32_t)g.n[3]), dim3(RB), 0, st, partial, nb, 1.0 / (2.0 * V3),
                            1.0 / (6.0 * V3), out);
     } else {
         const uint32_t nb = 2 * su2_blocks(g);
-        hipLaunchKernelGGL((k_su2_measure<R, NDIR_LANDAU>), dim3(nb, 1), dim3(RB), 0, st, f, g, partial);
+        hipLaunchKernelGGL((k_su2_measure<R, NDIR_LANDAU>), dim3(nb), dim3(RB), 0, st, f, g, nb, partial);
         const double V = 2.0 * (double)g.vh;
         hipLaunchKernelGGL(k_su2_finalize, dim3(1), dim3(RB), 0, st, partial, nb, 1.0 / (2.0 * V), 1.0 / (8.0 * V),
                            out);
@@ -344,7 +348,7 @@ template <typename R>
 hipError_t plaquette_impl(const Su2Field<R>& f, const Geom& g, double* partial, double* out, hipStream_t st)
 {
     const uint32_t nb = su2_blocks(g);
-    hipLaunchKernelGGL((k_su2_plaquette<R>), dim3(nb, 2), dim3(RB), 0, st, f, g, partial);
+    hipLaunchKernelGGL((k_su2_plaquette<R>), dim3(2 * nb), dim3(RB), 0, st, f, g, partial);
     const double V = 2.0 * (double)g.vh;
     hipLaunchKernelGGL(k_su2_finalize, dim3(1), dim3(RB), 0, st, partial, 2 * nb, 1.0 / (12.0 * V), 0.0, out);
     return hipGetLastError();
