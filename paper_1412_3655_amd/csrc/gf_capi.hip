@@ -434,13 +434,18 @@ gf_status upload_canonical(gf_lattice L, const double* dev_canon)
         L->anneal_sweeps = 0;
         return GF_OK;
     }
-    if (L->f32 && L->min8)
+    const uint64_t nlinks = (uint64_t)L->volume * 4;
+    if (L->prec == GF_MIXED && L->min8)
+        GF_HIP(gf::launch_pack_mixed(dev_canon, field8f(L), field64(L), L->geom, 0, nlinks, L->stream));
+    else if (L->prec == GF_MIXED)
+        GF_HIP(gf::launch_pack_mixed(dev_canon, field32(L), field64(L), L->geom, 0, nlinks, L->stream));
+    else if (L->f32 && L->min8)
         GF_HIP(gf::launch_pack(dev_canon, field8f(L), L->geom, L->stream));
     else if (L->f32)
         GF_HIP(gf::launch_pack(dev_canon, field32(L), L->geom, L->stream));
-    if (L->f64 && min8_64(L))
+    else if (min8_64(L))
         GF_HIP(gf::launch_pack(dev_canon, field8(L), L->geom, L->stream));
-    else if (L->f64)
+    else
         GF_HIP(gf::launch_pack(dev_canon, field64(L), L->geom, L->stream));
     if (L->gacc.base) GF_HIP(gf::launch_g_identity(L->gacc, L->geom, L->stream));
     L->phase = 0;

@@ -151,8 +151,6 @@ hipError_t launch_measure_slices(const Link8Field32& f, const Geom& g, double* p
 hipError_t launch_plaquette(const Link8Field32& f, const Geom& g, double* partial, double* out, hipStream_t st);
 hipError_t launch_pack(const double* canon, const Link8Field32& f, const Geom& g, hipStream_t st);
 hipError_t launch_unpack(const Link8Field32& f, const Geom& g, double* canon, hipStream_t st);
-hipError_t launch_pack_range(const double* canon, const Link8Field32& f, const Geom& g, uint64_t first, uint64_t n,
-                             hipStream_t st);
 hipError_t launch_unpack_range(const Link8Field32& f, const Geom& g, double* canon, uint64_t first, uint64_t n,
                                hipStream_t st);
 
@@ -170,15 +168,21 @@ hipError_t launch_unpack(const LinkField<double>& f, const Geom& g, double* cano
 hipError_t launch_unpack(const LinkField<float>& f, const Geom& g, double* canon, hipStream_t st);
 // The same for the canonical links first .. first+n-1 (4 per site, lexicographic
 // site order), held at canon[0 .. 18 n): a lattice moves through a staging
-// buffer smaller than itself.  The range must lie inside the lattice.
+// buffer smaller than itself.  The range must lie inside the lattice and hold
+// whole pairs of sites (first and n multiples of 8).
 hipError_t launch_pack_range(const double* canon, const LinkField<double>& f, const Geom& g, uint64_t first,
-                             uint64_t n, hipStream_t st);
-hipError_t launch_pack_range(const double* canon, const LinkField<float>& f, const Geom& g, uint64_t first,
                              uint64_t n, hipStream_t st);
 hipError_t launch_unpack_range(const LinkField<double>& f, const Geom& g, double* canon, uint64_t first, uint64_t n,
                                hipStream_t st);
 hipError_t launch_unpack_range(const LinkField<float>& f, const Geom& g, double* canon, uint64_t first, uint64_t n,
                                hipStream_t st);
+
+// Links first .. first+n-1 into the float32 and the float64 field of a GF_MIXED
+// lattice in one pass (the same bits as a pack of each).
+hipError_t launch_pack_mixed(const double* canon, const LinkField<float>& f32, const LinkField<double>& f64,
+                             const Geom& g, uint64_t first, uint64_t n, hipStream_t st);
+hipError_t launch_pack_mixed(const double* canon, const Link8Field32& f32, const LinkField<double>& f64,
+                             const Geom& g, uint64_t first, uint64_t n, hipStream_t st);
 
 // Mixed precision: g(x) <- 1; Gram-Schmidt of g; and the float64 rebuild
 // U_mu(x) <- g(x) U0_mu(x) g(x+mu^)^dag in place over the float64 field that

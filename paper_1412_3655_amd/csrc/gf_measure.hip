@@ -286,67 +286,88 @@ __global__ void __launch_bounds__(RBLOCK) k_rebuild_from_g(LinkField<double> u0,
     store_rows01(u0, parity, mu, h, u);
 }
 
-// canonical lex site s, direction mu -> (colour, half index)
-__device__ __forceinline__ void lex_to_half(const Geom& g, uint32_t s, int* parity, uint32_t* h)
+// Canonical links [site][mu][3][3][re,im] <-> a link field.  A block takes 64
+// consecutive sites (lexicographic): the canonical side is read or written in
+// order through LDS, and wave mu handles the links U_mu of the sites' 32 half
+// indices of either colour, two 512-byte runs per chunk of the field.  With one
+// thread per link instead, the canonical side went in 144-byte strides and unpack
+// reached 3.7 TB/s; both directions are now bound by their bytes (1.01 GB for
+// 32^4 float64: pack 195, unpack 272 -> 160).  A site's row in LDS is
+// padded to 74 doubles, which spreads the 64 sites of a column over the banks.
+constexpr uint32_t kCanonSites = 64;
+constexpr uint32_t kCanonRow = 74;
+
+// 16 bytes at the alignment of a double (the caller's array may have no more)
+typedef double canon2 __attribute__((ext_vector_type(2), aligned(8)));
+
+// The link of a thread in its block's tile of `left` sites from site `first` on
+// (even); false: none.
+struct CanonLink {
+    int parity, mu;
+    uint32_t h;
+    double2* row;  // its 9 entries in LDS
+};
+
+__device__ __forceinline__ bool canon_link(const Geom& g, uint32_t first, uint32_t left, double* rows, CanonLink& l)
 {
-    uint32_t x = s % (uint32_t)g.n[0];
-    uint32_t r = s / (uint32_t)g.n[0];
-    uint32_t y = r % (uint32_t)g.n[1];
-    r /= (uint32_t)g.n[1];
-    uint32_t z = r % (uint32_t)g.n[2];
-    uint32_t t = r / (uint32_t)g.n[2];
-    *parity = (int)((x + y + z + t) & 1u);
-    *h = s >> 1;
+    const uint32_t hh = threadIdx.x & 31u;
+    if (2 * hh >= left) return false;
+    l.mu = (int)(threadIdx.x >> 6);
+    l.parity = (int)(threadIdx.x >> 5) & 1;
+    l.h = first / 2 + hh;
+    const Site s = decode_site(g, l.parity, l.h);
+    l.row = (double2*)(rows + (2 * hh + (uint32_t)(s.x & 1)) * kCanonRow + l.mu * 18);
+    return true;
 }
 
-// R: the field's real type; Field: 12-real LinkField<R> or 8-real Link8Field
-// (rows 0 and 1 of the canonical link are encoded).  Links first .. first+n-1
-// (canonical order, 4 per site), read from canon[0 .. 18 n).
-template <typename R, typename Field>
-__global__ void __launch_bounds__(RBLOCK) k_pack(const double* canon, Field f, Geom g, uint64_t first, uint64_t n)
+// Sites first .. first+n-1 (first and n even) read from canon[0 .. 72 n).  MIXED:
+// both fields of a GF_MIXED lattice from one read (32^4, float32 links in 8
+// reals: 331 us in two passes -> 217).
+template <bool MIXED, typename Field>
+__global__ void __launch_bounds__(RBLOCK) k_pack(const double* canon, Field f, LinkField<double> f64, Geom g,
+                                                 uint32_t first, uint32_t n)
 {
-    const uint64_t i = (uint64_t)blockIdx.x * RBLOCK + threadIdx.x;
-    if (i >= n) return;
-    const uint64_t gid = first + i;
-    const uint32_t s = (uint32_t)(gid >> 2);
-    const int mu = (int)(gid & 3);
-    int parity;
-    uint32_t h;
-    lex_to_half(g, s, &parity, &h);
-    const double* src = canon + i * 18;
-    M3<R> u;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            u.re[i][j] = (R)src[(i * 3 + j) * 2];
-            u.im[i][j] = (R)src[(i * 3 + j) * 2 + 1];
-        }
-    store_link(f, parity, mu, h, u);
-}
-
-// Links first .. first+n-1 written to canon[0 .. 18 n).
-template <typename Field>
-__global__ void __launch_bounds__(RBLOCK) k_unpack(Field f, Geom g, double* canon, uint64_t first, uint64_t n)
-{
-    const uint64_t i = (uint64_t)blockIdx.x * RBLOCK + threadIdx.x;
-    if (i >= n) return;
-    const uint64_t gid = first + i;
-    const uint32_t s = (uint32_t)(gid >> 2);
-    const int mu = (int)(gid & 3);
-    int parity;
-    uint32_t h;
-    lex_to_half(g, s, &parity, &h);
+    __shared__ __align__(16) double rows[kCanonSites * kCanonRow];
+    const uint32_t done = blockIdx.x * kCanonSites;  // < n
+    const uint32_t left = n - done < kCanonSites ? n - done : kCanonSites;
+    const canon2* src = (const canon2*)(canon + (size_t)done * 72);
+    for (uint32_t q = threadIdx.x; q < left * 36; q += RBLOCK) {
+        const canon2 v = src[q];
+        ((double2*)rows)[q / 36 * (kCanonRow / 2) + q % 36] = make_double2(v.x, v.y);
+    }
+    __syncthreads();
+    CanonLink l;
+    if (!canon_link(g, first + done, left, rows, l)) return;
     M3<double> u;
-    load_full_f64(f, parity, mu, h, u);
-    double* dst = canon + i * 18;
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+    for (int e = 0; e < 6; ++e) {
+        u.re[e / 3][e % 3] = l.row[e].x;
+        u.im[e / 3][e % 3] = l.row[e].y;
+    }
+    store_link(f, l.parity, l.mu, l.h, u);
+    if constexpr (MIXED) store_link(f64, l.parity, l.mu, l.h, u);
+}
+
+// Sites first .. first+n-1 (first and n even) written to canon[0 .. 72 n).
+template <typename Field>
+__global__ void __launch_bounds__(RBLOCK) k_unpack(Field f, Geom g, double* canon, uint32_t first, uint32_t n)
+{
+    __shared__ __align__(16) double rows[kCanonSites * kCanonRow];
+    const uint32_t done = blockIdx.x * kCanonSites;  // < n
+    const uint32_t left = n - done < kCanonSites ? n - done : kCanonSites;
+    CanonLink l;
+    if (canon_link(g, first + done, left, rows, l)) {
+        M3<double> u;
+        load_full_f64(f, l.parity, l.mu, l.h, u);
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            dst[(i * 3 + j) * 2] = u.re[i][j];
-            dst[(i * 3 + j) * 2 + 1] = u.im[i][j];
-        }
+        for (int e = 0; e < 9; ++e) l.row[e] = make_double2(u.re[e / 3][e % 3], u.im[e / 3][e % 3]);
+    }
+    __syncthreads();
+    canon2* out = (canon2*)(canon + (size_t)done * 72);
+    for (uint32_t q = threadIdx.x; q < left * 36; q += RBLOCK) {
+        const double2 v = ((const double2*)rows)[q / 36 * (kCanonRow / 2) + q % 36];
+        out[q] = canon2{v.x, v.y};
+    }
 }
 
 // Every link of one field written into another of the other storage (12-real
@@ -412,17 +433,30 @@ hipError_t reunit_impl(const LinkField<R>& f, const Geom& g, hipStream_t st)
     return hipGetLastError();
 }
 
-// n = 0 stands for every link of the lattice; a range must lie inside it.
-template <typename R, typename Field>
-hipError_t pack_impl(const double* canon, const Field& f, const Geom& g, hipStream_t st, uint64_t first = 0,
-                     uint64_t n = 0)
+// Sites of the links first .. first + n - 1 (n = 0 with first = 0: all links) of
+// a lattice; false if the range leaves it or holds no whole pairs of sites (Nx is
+// even, so a pair is the two sites of one half index).
+bool canon_range(const Geom& g, uint64_t first, uint64_t n, uint32_t* first_site, uint32_t* sites)
 {
     const uint64_t nlinks = (uint64_t)g.vh * 8;
     if (n == 0 && first == 0) n = nlinks;
-    if (first > nlinks || n > nlinks - first) return hipErrorInvalidValue;
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL((k_pack<R, Field>), dim3((uint32_t)((n + RBLOCK - 1) / RBLOCK)), dim3(RBLOCK), 0, st, canon, f,
-                       g, first, n);
+    if (first > nlinks || n > nlinks - first || first % 8 || n % 8) return false;
+    *first_site = (uint32_t)(first / 4);
+    *sites = (uint32_t)(n / 4);
+    return true;
+}
+
+const LinkField<double> kNoField{nullptr, 0};
+
+template <bool MIXED, typename Field>
+hipError_t pack_impl(const double* canon, const Field& f, const LinkField<double>& f64, const Geom& g, hipStream_t st,
+                     uint64_t first = 0, uint64_t n = 0)
+{
+    uint32_t s0 = 0, sites = 0;
+    if (!canon_range(g, first, n, &s0, &sites)) return hipErrorInvalidValue;
+    if (sites == 0) return hipSuccess;
+    hipLaunchKernelGGL((k_pack<MIXED, Field>), dim3((sites + kCanonSites - 1) / kCanonSites), dim3(RBLOCK), 0, st,
+                       canon, f, f64, g, s0, sites);
     return hipGetLastError();
 }
 
@@ -430,12 +464,11 @@ template <typename Field>
 hipError_t unpack_impl(const Field& f, const Geom& g, double* canon, hipStream_t st, uint64_t first = 0,
                        uint64_t n = 0)
 {
-    const uint64_t nlinks = (uint64_t)g.vh * 8;
-    if (n == 0 && first == 0) n = nlinks;
-    if (first > nlinks || n > nlinks - first) return hipErrorInvalidValue;
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL((k_unpack<Field>), dim3((uint32_t)((n + RBLOCK - 1) / RBLOCK)), dim3(RBLOCK), 0, st, f, g,
-                       canon, first, n);
+    uint32_t s0 = 0, sites = 0;
+    if (!canon_range(g, first, n, &s0, &sites)) return hipErrorInvalidValue;
+    if (sites == 0) return hipSuccess;
+    hipLaunchKernelGGL((k_unpack<Field>), dim3((sites + kCanonSites - 1) / kCanonSites), dim3(RBLOCK), 0, st, f, g,
+                       canon, s0, sites);
     return hipGetLastError();
 }
 
@@ -527,11 +560,11 @@ hipError_t launch_reunitarize(const LinkField<float>& f, const Geom& g, hipStrea
 }
 hipError_t launch_pack(const double* c, const LinkField<double>& f, const Geom& g, hipStream_t st)
 {
-    return pack_impl<double>(c, f, g, st);
+    return pack_impl<false>(c, f, kNoField, g, st);
 }
 hipError_t launch_pack(const double* c, const LinkField<float>& f, const Geom& g, hipStream_t st)
 {
-    return pack_impl<float>(c, f, g, st);
+    return pack_impl<false>(c, f, kNoField, g, st);
 }
 hipError_t launch_unpack(const LinkField<double>& f, const Geom& g, double* c, hipStream_t st)
 {
@@ -544,12 +577,7 @@ hipError_t launch_unpack(const LinkField<float>& f, const Geom& g, double* c, hi
 hipError_t launch_pack_range(const double* c, const LinkField<double>& f, const Geom& g, uint64_t first, uint64_t n,
                              hipStream_t st)
 {
-    return n ? pack_impl<double>(c, f, g, st, first, n) : hipSuccess;
-}
-hipError_t launch_pack_range(const double* c, const LinkField<float>& f, const Geom& g, uint64_t first, uint64_t n,
-                             hipStream_t st)
-{
-    return n ? pack_impl<float>(c, f, g, st, first, n) : hipSuccess;
+    return n ? pack_impl<false>(c, f, kNoField, g, st, first, n) : hipSuccess;
 }
 hipError_t launch_unpack_range(const LinkField<double>& f, const Geom& g, double* c, uint64_t first, uint64_t n,
                                hipStream_t st)
@@ -560,6 +588,17 @@ hipError_t launch_unpack_range(const LinkField<float>& f, const Geom& g, double*
                                hipStream_t st)
 {
     return n ? unpack_impl(f, g, c, st, first, n) : hipSuccess;
+}
+
+hipError_t launch_pack_mixed(const double* c, const LinkField<float>& f32, const LinkField<double>& f64,
+                             const Geom& g, uint64_t first, uint64_t n, hipStream_t st)
+{
+    return n ? pack_impl<true>(c, f32, f64, g, st, first, n) : hipSuccess;
+}
+hipError_t launch_pack_mixed(const double* c, const Link8Field32& f32, const LinkField<double>& f64, const Geom& g,
+                             uint64_t first, uint64_t n, hipStream_t st)
+{
+    return n ? pack_impl<true>(c, f32, f64, g, st, first, n) : hipSuccess;
 }
 
 hipError_t launch_measure(const Link8Field& f, const Geom& g, double* p, double* o, hipStream_t st)
@@ -576,7 +615,7 @@ hipError_t launch_plaquette(const Link8Field& f, const Geom& g, double* p, doubl
 }
 hipError_t launch_pack(const double* c, const Link8Field& f, const Geom& g, hipStream_t st)
 {
-    return pack_impl<double>(c, f, g, st);
+    return pack_impl<false>(c, f, kNoField, g, st);
 }
 hipError_t launch_unpack(const Link8Field& f, const Geom& g, double* c, hipStream_t st)
 {
@@ -610,16 +649,11 @@ hipError_t launch_plaquette(const Link8Field32& f, const Geom& g, double* p, dou
 }
 hipError_t launch_pack(const double* c, const Link8Field32& f, const Geom& g, hipStream_t st)
 {
-    return pack_impl<double>(c, f, g, st);
+    return pack_impl<false>(c, f, kNoField, g, st);
 }
 hipError_t launch_unpack(const Link8Field32& f, const Geom& g, double* c, hipStream_t st)
 {
     return unpack_impl(f, g, c, st);
-}
-hipError_t launch_pack_range(const double* c, const Link8Field32& f, const Geom& g, uint64_t first, uint64_t n,
-                             hipStream_t st)
-{
-    return n ? pack_impl<double>(c, f, g, st, first, n) : hipSuccess;
 }
 hipError_t launch_unpack_range(const Link8Field32& f, const Geom& g, double* c, uint64_t first, uint64_t n,
                                hipStream_t st)

@@ -781,10 +781,11 @@ gf_status upload_job(gf_pool P, gf_lattice L, const double* host)
         const uint64_t n = std::min<uint64_t>(kStageLinks, nlinks - first);
         e = hipMemcpyAsync(P->stage, host + first * 18, n * 18 * sizeof(double), hipMemcpyHostToDevice, P->xfer);
         if (e == hipSuccess && L->f32 && L->min8)
-            e = gf::launch_pack_range(P->stage, field8f(L), L->geom, first, n, P->xfer);
+            e = gf::launch_pack_mixed(P->stage, field8f(L), field64(L), L->geom, first, n, P->xfer);
         else if (e == hipSuccess && L->f32)
-            e = gf::launch_pack_range(P->stage, field32(L), L->geom, first, n, P->xfer);
-        if (e == hipSuccess && L->f64) e = gf::launch_pack_range(P->stage, field64(L), L->geom, first, n, P->xfer);
+            e = gf::launch_pack_mixed(P->stage, field32(L), field64(L), L->geom, first, n, P->xfer);
+        else if (e == hipSuccess)
+            e = gf::launch_pack_range(P->stage, field64(L), L->geom, first, n, P->xfer);
     }
     if (e == hipSuccess && L->gacc.base) e = gf::launch_g_identity(L->gacc, L->geom, P->xfer);
     const hipError_t es = hipStreamSynchronize(P->xfer);  // also after a failed enqueue: nothing stays queued

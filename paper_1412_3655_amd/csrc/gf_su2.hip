@@ -248,26 +248,38 @@ __global__ void __launch_bounds__(RB) k_su2_pack(const double* canon, Su2Field<R
     store_q<false>(f, parity, mu, h, Quat<R>{(R)q0, (R)q1, (R)q2, (R)q3});
 }
 
+// 64 consecutive sites per block: wave mu reads the links U_mu of their 32 half
+// indices of either colour, and the block writes the canonical links in order
+// from LDS (as the SU(3) unpack; 32^3x64 float64 222 -> 132 us for 0.81 GB).  A
+// site's row in LDS is padded to 34 doubles.
+constexpr uint32_t kUnpackSites = 64;
+constexpr uint32_t kUnpackRow = 34;
+typedef double canon2 __attribute__((ext_vector_type(2), aligned(8)));  // at the alignment of a double
+
 template <typename R>
 __global__ void __launch_bounds__(RB) k_su2_unpack(Su2Field<R> f, Geom g, double* canon)
 {
-    const uint64_t gid = (uint64_t)blockIdx.x * RB + threadIdx.x;
-    if (gid >= (uint64_t)g.vh * 8) return;
-    const uint32_t s = (uint32_t)(gid / 4);
-    const int mu = (int)(gid % 4);
-    int parity;
-    uint32_t h;
-    lex_half(g, s, &parity, &h);
-    const Quat<R> q = load_q<false>(f, parity, mu, h);
-    double* u = canon + gid * 8;
-    u[0] = (double)q.b0;
-    u[1] = (double)q.b3;
-    u[2] = (double)q.b2;
-    u[3] = (double)q.b1;
-    u[4] = -(double)q.b2;
-    u[5] = (double)q.b1;
-    u[6] = (double)q.b0;
-    u[7] = -(double)q.b3;
+    __shared__ __align__(16) double row[kUnpackSites * kUnpackRow];
+    const uint32_t sites = 2 * g.vh, done = blockIdx.x * kUnpackSites;  // < sites
+    const uint32_t left = sites - done < kUnpackSites ? sites - done : kUnpackSites;
+    const int mu = (int)(threadIdx.x >> 6), parity = (int)(threadIdx.x >> 5) & 1;
+    const uint32_t hh = threadIdx.x & 31u;
+    if (2 * hh < left) {
+        const uint32_t h = done / 2 + hh;
+        const Site s = decode_site(g, parity, h);
+        const Quat<R> q = load_q<false>(f, parity, mu, h);
+        double2* u = (double2*)(row + (2 * hh + (uint32_t)(s.x & 1)) * kUnpackRow + mu * 8);
+        u[0] = make_double2((double)q.b0, (double)q.b3);
+        u[1] = make_double2((double)q.b2, (double)q.b1);
+        u[2] = make_double2(-(double)q.b2, (double)q.b1);
+        u[3] = make_double2((double)q.b0, -(double)q.b3);
+    }
+    __syncthreads();
+    canon2* out = (canon2*)(canon + (size_t)done * 32);
+    for (uint32_t k = threadIdx.x; k < left * 16; k += RB) {
+        const double2 v = ((const double2*)row)[k / 16 * (kUnpackRow / 2) + k % 16];
+        out[k] = canon2{v.x, v.y};
+    }
 }
 
 template <typename R, int MODE, int NDIR>
@@ -436,13 +448,13 @@ hipError_t launch_su2_pack(const double* canon, const Su2Field<float>& f, const 
 }
 hipError_t launch_su2_unpack(const Su2Field<double>& f, const Geom& g, double* canon, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_su2_unpack<double>), dim3((uint32_t)(((uint64_t)g.vh * 8 + RB - 1) / RB)), dim3(RB), 0,
+    hipLaunchKernelGGL((k_su2_unpack<double>), dim3((2 * g.vh + kUnpackSites - 1) / kUnpackSites), dim3(RB), 0,
                        st, f, g, canon);
     return hipGetLastError();
 }
 hipError_t launch_su2_unpack(const Su2Field<float>& f, const Geom& g, double* canon, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_su2_unpack<float>), dim3((uint32_t)(((uint64_t)g.vh * 8 + RB - 1) / RB)), dim3(RB), 0,
+    hipLaunchKernelGGL((k_su2_unpack<float>), dim3((2 * g.vh + kUnpackSites - 1) / kUnpackSites), dim3(RB), 0,
                        st, f, g, canon);
     return hipGetLastError();
 }
