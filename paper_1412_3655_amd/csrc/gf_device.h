@@ -533,29 +533,27 @@ struct Quat {
     R b0, b1, b2, b3;
 };
 
-// The power g^omega of the exact overrelaxation rule as two polynomials.
+// The power g^omega of the exact overrelaxation rule in float64 as two polynomials.
 //
 // For an angle psi in [0, pi/4] and y = 1 - cos psi, cos(omega psi) = 1 - y P(y)
 // and sin(omega psi) = Q(y) sin psi, where P and Q are analytic in y up to
 // y = 2 (P and Q are (1 - T_omega(1 - y)) / y and U_{omega-1}(1 - y), the
 // Chebyshev functions of real order), so over [0, 1 - 1/sqrt 2] their
 // interpolants at Chebyshev nodes converge by a factor of about 25 a term: 11
-// coefficients reach 1e-16, 5 reach 4e-8.  They depend on omega alone; the host
-// computes them once per omega (make_or_omega) and the kernel holds them in scalar registers.
+// coefficients reach 1e-16.  They depend on omega alone; the host computes them
+// once per omega (make_or_omega) and the kernel holds them in scalar registers.
 // c_mid = cos(omega pi/2), s_mid = sin(omega pi/2), c_far = cos(omega pi),
 // s_far = sin(omega pi) carry the angles beyond pi/4 back to that range.
-template <typename R>
 struct OrPower {
-    static constexpr int N = sizeof(R) == 8 ? 11 : 5;
-    R p[N], q[N];
-    R c_mid, s_mid, c_far, s_far;
+    static constexpr int N = 11;
+    double p[N], q[N];
+    double c_mid, s_mid, c_far, s_far;
 };
 
-// omega with its power in both precisions (make_or_omega, 1 <= omega < 2).
+// omega with its power (make_or_omega, 1 <= omega < 2).
 struct OrOmega {
     double omega;
-    OrPower<double> p64;
-    OrPower<float> p32;
+    OrPower power;
 };
 
 OrOmega make_or_omega(double omega);

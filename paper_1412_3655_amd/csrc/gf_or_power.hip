@@ -41,10 +41,9 @@ void interpolate(const long double (&x)[N], long double (&f)[N], long double (&m
     }
 }
 
-template <typename R>
-void make_power(long double w, OrPower<R>* out)
+void make_power(long double w, OrPower* out)
 {
-    constexpr int N = OrPower<R>::N;
+    constexpr int N = OrPower::N;
     const long double top = 1.0L - sqrtl(0.5L);  // y at psi = pi/4
     long double x[N], fp[N], fq[N], p[N], q[N];
     for (int i = 0; i < N; ++i) {
@@ -54,13 +53,13 @@ void make_power(long double w, OrPower<R>* out)
     interpolate<N>(x, fp, p);
     interpolate<N>(x, fq, q);
     for (int k = 0; k < N; ++k) {
-        out->p[k] = (R)p[k];
-        out->q[k] = (R)q[k];
+        out->p[k] = (double)p[k];
+        out->q[k] = (double)q[k];
     }
-    out->c_mid = (R)cosl(0.5L * kPi * w);
-    out->s_mid = (R)sinl(0.5L * kPi * w);
-    out->c_far = (R)cosl(kPi * w);
-    out->s_far = (R)sinl(kPi * w);
+    out->c_mid = (double)cosl(0.5L * kPi * w);
+    out->s_mid = (double)sinl(0.5L * kPi * w);
+    out->c_far = (double)cosl(kPi * w);
+    out->s_far = (double)sinl(kPi * w);
 }
 
 }  // namespace
@@ -69,8 +68,7 @@ OrOmega make_or_omega(double omega)
 {
     OrOmega om{};
     om.omega = omega;
-    make_power(omega, &om.p64);
-    make_power(omega, &om.p32);
+    make_power(omega, &om.power);
     return om;
 }
 

@@ -66,8 +66,7 @@ struct SlotDev {
     GField gacc;
     Geom g;
     double omega;
-    OrPower<double> p64;  // of omega, for the float64 / float32 overrelaxation sweeps
-    OrPower<float> p32;
+    OrPower power;  // of omega
     double T0, T1;
     int32_t n_anneal;
     uint32_t key0, key1;
@@ -214,12 +213,9 @@ __global__ void __launch_bounds__(BLOCK) k_pool_sweep(const SlotDev* __restrict_
     Rule<R> rule;
     if constexpr (MODE == HEATBATH) {
         const uint32_t s = sd.anneal_base + k;
-        rule = Rule<R>{R(1), (R)schedule_T(sd, s), sd.key0, sd.key1, s, {}};
+        rule = hb_rule((R)schedule_T(sd, s), sd.key0, sd.key1, s);
     } else {
-        if constexpr (sizeof(R) == 8)
-            rule = Rule<R>{(R)sd.omega, R(1), 0u, 0u, 0u, sd.p64};
-        else
-            rule = Rule<R>{(R)sd.omega, R(1), 0u, 0u, 0u, sd.p32};
+        rule = or_rule<R>(sd.omega, sd.power);
     }
     if constexpr (M8)
         site_update<R, TPS, MODE, TRACKG, CP, NDIR_LANDAU, Link8Field32>(field8_of(sd), sd.g, parity, h, r, rule,
@@ -679,8 +675,7 @@ void fill_slot(gf_pool P, int slot)
     d.g = L->geom;
     const OrOmega& om = or_omega(L, j.p.omega);
     d.omega = om.omega;
-    d.p64 = om.p64;
-    d.p32 = om.p32;
+    d.power = om.power;
     d.T0 = j.T0;
     d.T1 = j.T1;
     d.n_anneal = j.anneal_total;

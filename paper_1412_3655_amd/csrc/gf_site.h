@@ -32,28 +32,42 @@ namespace gf {
 constexpr int OR_EXACT = 0;
 constexpr int HEATBATH = 2;
 
-// Parameters of the subgroup rule: omega and its power for overrelaxation;
-// temperature T, Philox key and sweep counter for the heat bath.
+// Parameters of the subgroup rule: omega and, for the exact float64 power, its
+// coefficients for overrelaxation; temperature T, Philox key and sweep counter
+// for the heat bath.
 template <typename R>
-struct Rule {
-    R omega;
-    R T;
+struct Rule;
+template <>
+struct Rule<double> {
+    double omega, T;
     uint32_t key0, key1, sweep;
-    OrPower<R> pw;
+    OrPower power;
+};
+template <>
+struct Rule<float> {
+    float omega, T;
+    uint32_t key0, key1, sweep;
+    float power;  // omega
 };
 
-// The overrelaxation rule of an omega (host).
+// The overrelaxation rule of an omega, the heat-bath rule of a temperature, key and sweep.
 template <typename R>
-inline Rule<R> or_rule(const OrOmega& om)
+__host__ __device__ __forceinline__ Rule<R> or_rule(double omega, const OrPower& power)
 {
     if constexpr (sizeof(R) == 8)
-        return Rule<R>{om.omega, R(1), 0u, 0u, 0u, om.p64};
+        return Rule<R>{omega, 1.0, 0u, 0u, 0u, power};
     else
-        return Rule<R>{(R)om.omega, R(1), 0u, 0u, 0u, om.p32};
+        return Rule<R>{(float)omega, 1.0f, 0u, 0u, 0u, (float)omega};
+}
+
+template <typename R>
+__host__ __device__ __forceinline__ Rule<R> hb_rule(R T, uint32_t key0, uint32_t key1, uint32_t sweep)
+{
+    return Rule<R>{R(1), T, key0, key1, sweep, {}};
 }
 
 // 1/sqrt(x) to about one unit in the last place for normal x far from overflow:
-// the hardware seed and one third-order (float64) or second-order (float32) step.
+// the hardware seed and one third-order step.
 __device__ __forceinline__ double rsqrt_of(double x)
 {
     const double y = __builtin_amdgcn_rsq(x);
@@ -61,18 +75,112 @@ __device__ __forceinline__ double rsqrt_of(double x)
     return fmad(y * e, fmad(e, 0.375, 0.5), y);
 }
 
-__device__ __forceinline__ float rsqrt_of(float x)
+// Squares below this leave the range of rsqrt_of.
+constexpr double kTinySquare = 0x1p-960;
+
+// The principal power of a float64 quaternion (see or_element) without its angle
+// (see OrPower): sin^2 psi comes straight from a, so y has a small relative
+// error and no cancellation.  A block with 0 <= phi <= pi/4, which is every
+// block of a configuration near its maximum, needs one reciprocal square root,
+// one reciprocal and the two polynomials; phi in (pi/4, 3pi/4] is measured from
+// pi/2 and phi > 3pi/4 from pi, in a branch that a wave skips when no lane needs
+// it.  Against atan2 and sincos of the device library a wave of the sweep at 4
+// lanes per site issues 811 vector instructions instead of about 1400; the 8^4
+// sweep, which a chain of dependent operations bounds, went from 11.8 to 10.0
+// us, 16^4 from 20.0 to 17.7.  The error against values of higher precision is
+// smaller at every angle (rms, in 2^-53: 0.3 and 0.3 near the maximum, 1.2 and
+// 1.3 over random blocks; atan2 and sincos second).
+__device__ __forceinline__ Quat<double> or_power(const Quat<double>& a, const OrPower& w)
 {
-    const float y = __builtin_amdgcn_rsqf(x);
-    const float e = fmad(-(x * y), y, 1.0f);
-    return fmad(y * e, 0.5f, y);
+    Quat<double> b;
+    double a0 = a.b0, x1 = a.b1, x2 = a.b2, x3 = a.b3;
+    double v2 = fmad(x1, x1, fmad(x2, x2, x3 * x3));
+    double a02 = a0 * a0;
+    double n2 = a02 + v2;
+    if (n2 < kTinySquare) {  // b does not depend on the scale of a
+        constexpr double up = 0x1p+600;
+        a0 *= up;
+        x1 *= up;
+        x2 *= up;
+        x3 *= up;
+        v2 = fmad(x1, x1, fmad(x2, x2, x3 * x3));
+        a02 = a0 * a0;
+        n2 = a02 + v2;
+    }
+    const double rn = rsqrt_of(n2);
+    const bool near = a0 > 0.0 && a02 >= v2;
+    bool identity = false;
+    // psi is the angle of (big, small): cos psi = big rn, sin psi = small rn
+    double big = a0, small = 0.0, small2 = v2, c = 1.0, s = 0.0, iv = 0.0;
+    if (!near) {
+        double v;
+        if (v2 >= kTinySquare) {
+            iv = rsqrt_of(v2);
+            v = v2 * iv;
+        } else {
+            identity = !(v2 > 0.0);
+            v = sqrt(v2);
+            iv = 1.0 / v;
+        }
+        const bool mid = v2 > a02;
+        big = mid ? v : -a0;
+        small = mid ? a0 : v;
+        small2 = mid ? a02 : v2;
+        c = mid ? w.c_mid : w.c_far;
+        s = mid ? w.s_mid : w.s_far;
+    }
+    const double y = (small2 * rn) * (rn * recip(fmad(big, rn, 1.0)));
+    double p = w.p[OrPower::N - 1], q = w.q[OrPower::N - 1];
+#pragma unroll
+    for (int k = OrPower::N - 2; k >= 0; --k) {
+        p = fmad(p, y, w.p[k]);
+        q = fmad(q, y, w.q[k]);
+    }
+    const double cw = fmad(-y, p, 1.0);  // cos(omega psi)
+    const double sw = q * rn;            // sin(omega psi) / small
+    double f = -sw;
+    b.b0 = cw;
+    if (!near) {
+        const double sn = sw * small;
+        b.b0 = fmad(c, cw, s * sn);
+        f = -(fmad(s, cw, -(c * sn)) * iv);
+        if (identity) {
+            b.b0 = a.b0 < 0.0 ? -1.0 : 1.0;
+            f = x1 = x2 = x3 = 0.0;
+        }
+    }
+    b.b1 = f * x1;
+    b.b2 = f * x2;
+    b.b3 = f * x3;
+    return b;
 }
 
-// Squares below this leave the range of rsqrt_of.
-template <typename R>
-__device__ __forceinline__ constexpr R tiny_square()
+// The same through the device library's float32 functions.  (The polynomials
+// would save a float32 sweep of 8-real links about 10 % of its instructions, but
+// any other rounding of b moves float32 results by their own error, which rough
+// inputs amplify up to 1e-3 at single sites within ten sweeps; float32 runs stay
+// reproducible instead.)
+__device__ __forceinline__ Quat<float> or_power(const Quat<float>& a, float omega)
 {
-    return sizeof(R) == 8 ? (R)0x1p-960 : (R)0x1p-100f;
+    Quat<float> b;
+    const float v2 = fmad(a.b1, a.b1, fmad(a.b2, a.b2, a.b3 * a.b3));
+    if (v2 > 0.0f) {
+        const float v = sqrt(v2);
+        const float phi = atan2(v, a.b0);
+        float s, c;
+        sin_cos(omega * phi, &s, &c);
+        const float f = -s / v;
+        b.b0 = c;
+        b.b1 = f * a.b1;
+        b.b2 = f * a.b2;
+        b.b3 = f * a.b3;
+    } else {
+        b.b0 = a.b0 < 0.0f ? -1.0f : 1.0f;
+        b.b1 = 0.0f;
+        b.b2 = 0.0f;
+        b.b3 = 0.0f;
+    }
+    return b;
 }
 
 // The SU(2) element applied for the projected block quaternion a (unnormalised,
@@ -81,95 +189,22 @@ __device__ __forceinline__ constexpr R tiny_square()
 // (cos(omega phi), -sin(omega phi) a_vec/|a_vec|).  BINOMIAL1: normalise
 // (1 - omega) + omega b.  |a_vec| = 0 (EXACT) or |a| = 0 leaves the subgroup
 // alone (up to the sign of a0).
-//
-// EXACT is evaluated without the angle (see OrPower): sin^2 psi comes straight
-// from a, so y has a small relative error and no cancellation.  A block with
-// 0 <= phi <= pi/4, which is every block of a configuration near its maximum,
-// needs one reciprocal square root, one reciprocal and the two polynomials;
-// phi in (pi/4, 3pi/4] is measured from pi/2 and phi > 3pi/4 from pi, in a
-// branch that a wave skips when no lane needs it.  Against atan2 and sincos of
-// the device library a wave of the float64 sweep at 4 lanes per site issues 811
-// vector instructions instead of about 1400; the 8^4 sweep, which a chain of
-// dependent operations bounds, went from 11.8 to 10.0 us, 16^4 from 20.0 to 17.7,
-// and the 32^4 mixed sweep with 8-real links, which the instruction rate
-// bounds, from 128 to 118 us.  The error against values of higher precision is
-// smaller at every angle (float64 rms, in 2^-53: 0.3 and 0.3 near the maximum,
-// 1.2 and 1.3 over random blocks; atan2 and sincos second).
 template <int MODE, typename R>
 __device__ __forceinline__ Quat<R> or_element(const Quat<R>& a, const Rule<R>& rule)
 {
-    Quat<R> b;
     if constexpr (MODE == OR_EXACT) {
-        const OrPower<R>& w = rule.pw;
-        R a0 = a.b0, x1 = a.b1, x2 = a.b2, x3 = a.b3;
-        R v2 = fmad(x1, x1, fmad(x2, x2, x3 * x3));
-        R a02 = a0 * a0;
-        R n2 = a02 + v2;
-        if (n2 < tiny_square<R>()) {  // b does not depend on the scale of a
-            constexpr R up = sizeof(R) == 8 ? (R)0x1p+600 : (R)0x1p+100f;
-            a0 *= up;
-            x1 *= up;
-            x2 *= up;
-            x3 *= up;
-            v2 = fmad(x1, x1, fmad(x2, x2, x3 * x3));
-            a02 = a0 * a0;
-            n2 = a02 + v2;
-        }
-        const R rn = rsqrt_of(n2);
-        const bool near = a0 > R(0) && a02 >= v2;
-        bool identity = false;
-        // psi is the angle of (big, small): cos psi = big rn, sin psi = small rn
-        R big = a0, small = R(0), small2 = v2, c = R(1), s = R(0), iv = R(0);
-        if (!near) {
-            R v;
-            if (v2 >= tiny_square<R>()) {
-                iv = rsqrt_of(v2);
-                v = v2 * iv;
-            } else {
-                identity = !(v2 > R(0));
-                v = sqrt(v2);
-                iv = R(1) / v;
-            }
-            const bool mid = v2 > a02;
-            big = mid ? v : -a0;
-            small = mid ? a0 : v;
-            small2 = mid ? a02 : v2;
-            c = mid ? w.c_mid : w.c_far;
-            s = mid ? w.s_mid : w.s_far;
-        }
-        const R y = (small2 * rn) * (rn * recip(fmad(big, rn, R(1))));
-        R p = w.p[OrPower<R>::N - 1], q = w.q[OrPower<R>::N - 1];
-#pragma unroll
-        for (int k = OrPower<R>::N - 2; k >= 0; --k) {
-            p = fmad(p, y, w.p[k]);
-            q = fmad(q, y, w.q[k]);
-        }
-        const R cw = fmad(-y, p, R(1));  // cos(omega psi)
-        const R sw = q * rn;             // sin(omega psi) / small
-        R f = -sw;
-        b.b0 = cw;
-        if (!near) {
-            const R sn = sw * small;
-            b.b0 = fmad(c, cw, s * sn);
-            f = -(fmad(s, cw, -(c * sn)) * iv);
-            if (identity) {
-                b.b0 = a.b0 < R(0) ? R(-1) : R(1);
-                f = x1 = x2 = x3 = R(0);
-            }
-        }
-        b.b1 = f * x1;
-        b.b2 = f * x2;
-        b.b3 = f * x3;
+        return or_power(a, rule.power);
     } else {
+        Quat<R> b;
         const R omega = rule.omega;
         const R n2 = fmad(a.b0, a.b0, fmad(a.b1, a.b1, fmad(a.b2, a.b2, a.b3 * a.b3)));
         if (n2 > R(0)) {
-            const R inv = n2 >= tiny_square<R>() ? rsqrt_of(n2) : R(1) / sqrt(n2);
+            const R inv = R(1) / sqrt(n2);
             const R t0 = fmad(omega, a.b0 * inv, R(1) - omega);
             const R t1 = -omega * (a.b1 * inv);
             const R t2 = -omega * (a.b2 * inv);
             const R t3 = -omega * (a.b3 * inv);
-            const R tn = rsqrt_of(fmad(t0, t0, fmad(t1, t1, fmad(t2, t2, t3 * t3))));  // of a value >= 1
+            const R tn = R(1) / sqrt(fmad(t0, t0, fmad(t1, t1, fmad(t2, t2, t3 * t3))));
             b.b0 = t0 * tn;
             b.b1 = t1 * tn;
             b.b2 = t2 * tn;
@@ -180,8 +215,8 @@ __device__ __forceinline__ Quat<R> or_element(const Quat<R>& a, const Rule<R>& r
             b.b2 = R(0);
             b.b3 = R(0);
         }
+        return b;
     }
-    return b;
 }
 
 

@@ -318,7 +318,7 @@ template <typename R>
 hipError_t or_impl(const Su2Field<R>& f, const Geom& g, int parity, const OrOmega& om, int mode, const SweepConfig& c,
                    hipStream_t st, int gauge, double* est)
 {
-    const Rule<R> rule = or_rule<R>(om);
+    const Rule<R> rule = or_rule<R>(om.omega, om.power);
     return mode == OR_EXACT ? launch_gauge<R, 0>(f, g, parity, rule, c, st, gauge, est)
                             : launch_gauge<R, 1>(f, g, parity, rule, c, st, gauge, est);
 }
@@ -327,7 +327,7 @@ template <typename R>
 hipError_t hb_impl(const Su2Field<R>& f, const Geom& g, int parity, R T, uint64_t seed, uint32_t sweep,
                    const SweepConfig& c, hipStream_t st, int gauge)
 {
-    const Rule<R> rule{R(1), T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep, {}};
+    const Rule<R> rule = hb_rule(T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep);
     return launch_gauge<R, HEATBATH>(f, g, parity, rule, c, st, gauge, nullptr);
 }
 

@@ -149,7 +149,7 @@ hipError_t or_half_sweep(const LinkField<double>& f, const Geom& g, int parity, 
                          const SweepConfig& cfg, hipStream_t st, double* est)
 {
     const GField none{nullptr, 0};
-    const Rule<double> rule = or_rule<double>(om);
+    const Rule<double> rule = or_rule<double>(om.omega, om.power);
     return mode == OR_EXACT ? launch_mode<NDIR, EST, double, 0, false>(f, g, parity, rule, cfg, none, st, est)
                             : launch_mode<NDIR, EST, double, 1, false>(f, g, parity, rule, cfg, none, st, est);
 }
@@ -158,7 +158,7 @@ template <int NDIR, bool EST>
 hipError_t or_half_sweep(const LinkField<float>& f, const Geom& g, int parity, const OrOmega& om, int mode,
                          const SweepConfig& cfg, const GField& gacc, hipStream_t st, double* est)
 {
-    const Rule<float> rule = or_rule<float>(om);
+    const Rule<float> rule = or_rule<float>(om.omega, om.power);
     if (gacc.base)
         return mode == OR_EXACT ? launch_mode<NDIR, EST, float, 0, true>(f, g, parity, rule, cfg, gacc, st, est)
                                 : launch_mode<NDIR, EST, float, 1, true>(f, g, parity, rule, cfg, gacc, st, est);
@@ -171,7 +171,7 @@ hipError_t hb_half_sweep(const LinkField<double>& f, const Geom& g, int parity, 
                          uint32_t sweep, const SweepConfig& cfg, hipStream_t st)
 {
     const GField none{nullptr, 0};
-    const Rule<double> rule{1.0, T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep, {}};
+    const Rule<double> rule = hb_rule(T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep);
     return launch_mode<NDIR, false, double, HEATBATH, false>(f, g, parity, rule, cfg, none, st, nullptr);
 }
 
@@ -179,7 +179,7 @@ template <int NDIR>
 hipError_t hb_half_sweep(const LinkField<float>& f, const Geom& g, int parity, float T, uint64_t seed,
                          uint32_t sweep, const SweepConfig& cfg, const GField& gacc, hipStream_t st)
 {
-    const Rule<float> rule{1.0f, T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep, {}};
+    const Rule<float> rule = hb_rule(T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep);
     if (gacc.base) return launch_mode<NDIR, false, float, HEATBATH, true>(f, g, parity, rule, cfg, gacc, st, nullptr);
     return launch_mode<NDIR, false, float, HEATBATH, false>(f, g, parity, rule, cfg, gacc, st, nullptr);
 }
@@ -191,7 +191,7 @@ hipError_t or_half_sweep(const Link8Field& f, const Geom& g, int parity, const O
                          const SweepConfig& cfg, hipStream_t st, double* est)
 {
     const GField none{nullptr, 0};
-    const Rule<double> rule = or_rule<double>(om);
+    const Rule<double> rule = or_rule<double>(om.omega, om.power);
     return mode == OR_EXACT ? launch_mode<NDIR, EST, double, 0, false>(f, g, parity, rule, cfg, none, st, est)
                             : launch_mode<NDIR, EST, double, 1, false>(f, g, parity, rule, cfg, none, st, est);
 }
@@ -201,7 +201,7 @@ hipError_t hb_half_sweep(const Link8Field& f, const Geom& g, int parity, double 
                          const SweepConfig& cfg, hipStream_t st)
 {
     const GField none{nullptr, 0};
-    const Rule<double> rule{1.0, T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep, {}};
+    const Rule<double> rule = hb_rule(T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep);
     return launch_mode<NDIR, false, double, HEATBATH, false>(f, g, parity, rule, cfg, none, st, nullptr);
 }
 
@@ -211,7 +211,7 @@ template <int NDIR, bool EST>
 hipError_t or_half_sweep(const Link8Field32& f, const Geom& g, int parity, const OrOmega& om, int mode,
                          const SweepConfig& cfg, const GField& gacc, hipStream_t st, double* est)
 {
-    const Rule<float> rule = or_rule<float>(om);
+    const Rule<float> rule = or_rule<float>(om.omega, om.power);
     if (gacc.base)
         return mode == OR_EXACT ? launch_mode<NDIR, EST, float, 0, true>(f, g, parity, rule, cfg, gacc, st, est)
                                 : launch_mode<NDIR, EST, float, 1, true>(f, g, parity, rule, cfg, gacc, st, est);
@@ -223,7 +223,7 @@ template <int NDIR>
 hipError_t hb_half_sweep(const Link8Field32& f, const Geom& g, int parity, float T, uint64_t seed, uint32_t sweep,
                          const SweepConfig& cfg, const GField& gacc, hipStream_t st)
 {
-    const Rule<float> rule{1.0f, T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep, {}};
+    const Rule<float> rule = hb_rule(T, (uint32_t)seed, (uint32_t)(seed >> 32), sweep);
     if (gacc.base) return launch_mode<NDIR, false, float, HEATBATH, true>(f, g, parity, rule, cfg, gacc, st, nullptr);
     return launch_mode<NDIR, false, float, HEATBATH, false>(f, g, parity, rule, cfg, gacc, st, nullptr);
 }
