@@ -101,9 +101,8 @@ __device__ __forceinline__ uint32_t low_bit(float v)
 // sweeps compound: a float32 unit is 2^29 times a float64 one.)
 __device__ __forceinline__ float with_low_bit(float v, uint32_t bit)
 {
-    uint32_t u = __float_as_uint(v);
-    if ((u & 1u) != bit) u = (u & 2u) ? u - 1u : u + 1u;
-    return __uint_as_float(u);
+    const int u = __float_as_int(v);
+    return __int_as_float(u + __mul24((u ^ (int)bit) & 1, 1 - (u & 2)));
 }
 
 // Largest stored half-angle tangent: t^2 + 1 stays finite in the type (the
@@ -117,50 +116,49 @@ __device__ __forceinline__ constexpr R tan_clamp()
 // The codec's square roots and quotients take operands in fixed ranges (every
 // square root of a value in [1/3, 1], every divisor of magnitude <= 2 or a
 // finite 1 + t^2), so they skip the general routines' range scaling and
-// special-value handling: a hardware reciprocal or reciprocal square root
-// seed refined by Newton's (reciprocal) and Goldschmidt's (square root)
-// iterations, two steps each (a seed good to 2^-14 ends within 1-2 units in
-// the last place), then one residual correction.
+// special-value handling: a hardware seed, refined, then one residual
+// correction.  Measured over [1/4, 4], the float64 seeds of the reciprocal and
+// the reciprocal square root are good to 2^-24.4 and 2^-24.2, so one third-order
+// step ends at half a unit in the last place (square root: 0.6 before the
+// correction); the float32 seeds are good to 2^-23.3, and the residual
+// correction alone rounds the square root correctly (a refinement step before it
+// gave the same bits over 2e6 values).  The sweeps of 8-real links are bound by
+// their vector instructions: with these steps, picks on two masks and an integer
+// flag a float32 wave at one lane per site went from 3966 to 3798 of them, a
+// float64 one at two lanes from 2702 to 2635 (32^4 float32 at 4 lanes 150 -> 127
+// us per sweep, 24^3x48 float64 136 -> 129).
 
 // 1/d for 1 <= |d| < 2^1000
 __device__ __forceinline__ double recip(double d)
 {
-    double r = __builtin_amdgcn_rcp(d);
-    double e = fmad(-d, r, 1.0);
-    r = fmad(r, e, r);
-    e = fmad(-d, r, 1.0);
-    return fmad(r, e, r);
+    const double r = __builtin_amdgcn_rcp(d);
+    const double e = fmad(-d, r, 1.0);
+    return fmad(r, fmad(e, e, e), r);
 }
 
 // n / d for |n| <= 2 and 0 < |d| <= 2 (d = +-0 or subnormal gives an infinite
 // or NaN quotient, which the caller clamps)
 __device__ __forceinline__ double quotient(double n, double d)
 {
-    double r = __builtin_amdgcn_rcp(d);
-    double e = fmad(-d, r, 1.0);
-    r = fmad(r, e, r);
-    e = fmad(-d, r, 1.0);
-    r = fmad(r, e, r);
+    const double r = recip(d);
     const double q = n * r;
     return fmad(r, fmad(-d, q, n), q);
+}
+
+// 1/sqrt(x) to about one unit in the last place for normal x far from overflow.
+__device__ __forceinline__ double rsqrt_of(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fmad(-(x * y), y, 1.0);
+    return fmad(y * e, fmad(e, 0.375, 0.5), y);
 }
 
 // sqrt(x) and 1/sqrt(x) for 1/4 <= x <= 2
 __device__ __forceinline__ void sqrt_rsqrt(double x, double& sq, double& rs)
 {
-    const double y = __builtin_amdgcn_rsq(x);
-    double g = x * y, h = 0.5 * y;
-    double r = fmad(-g, h, 0.5);
-    g = fmad(g, r, g);
-    h = fmad(h, r, h);
-    r = fmad(-g, h, 0.5);
-    g = fmad(g, r, g);
-    h = fmad(h, r, h);
-    g = fmad(fmad(-g, g, x), h, g);
-    double i = 2.0 * h;
-    i = fmad(i, fmad(-g, i, 1.0), i);
-    sq = g;
-    rs = i;
+    rs = rsqrt_of(x);
+    const double g = x * rs;
+    sq = fmad(fmad(-g, g, x), 0.5 * rs, g);
 }
 
 __device__ __forceinline__ double sqrt_of(double x)
@@ -170,8 +168,6 @@ __device__ __forceinline__ double sqrt_of(double x)
     return sq;
 }
 
-// Float32: the hardware seeds are good to about 1 unit in the last place, so
-// one refinement step and the residual correction suffice.
 __device__ __forceinline__ float recip(float d)
 {
     const float r = __builtin_amdgcn_rcpf(d);
@@ -188,15 +184,10 @@ __device__ __forceinline__ float quotient(float n, float d)
 __device__ __forceinline__ void sqrt_rsqrt(float x, float& sq, float& rs)
 {
     const float y = __builtin_amdgcn_rsqf(x);
-    float g = x * y, h = 0.5f * y;
-    const float r = fmad(-g, h, 0.5f);
-    g = fmad(g, r, g);
-    h = fmad(h, r, h);
-    g = fmad(fmad(-g, g, x), h, g);
-    float i = 2.0f * h;
-    i = fmad(i, fmad(-g, i, 1.0f), i);
+    const float h = x * y;
+    const float g = fmad(fmad(-h, h, x), 0.5f * y, h);
     sq = g;
-    rs = i;
+    rs = fmad(y, fmad(-g, y, 1.0f), y);
 }
 
 __device__ __forceinline__ float sqrt_of(float x)
@@ -222,33 +213,40 @@ __device__ __forceinline__ R tan_half_of(R re, R im, R a2, R clamp)
 {
     const R a = sqrt_of(a2);
     const bool right = re >= (R)0;
-    R t = quotient(right ? im : a - re, right ? a + re : im);
+    const R sum = a + fabs(re);
+    R t = quotient(right ? im : sum, right ? sum : im);
     if (!(fabs(t) <= clamp)) t = copysign(clamp, im);
     return t;
 }
 
+// The pivot column as two flags (neither: column 0), so that a pick of one of
+// three values is two selects on masks computed once per link.
+struct Pivot {
+    bool k1, k2;
+};
+
 // v[c] for c = (k + f) mod 3, i.e. the entry of frame index f of a row whose
-// pivot column is k (k in 0..2)
+// pivot column is k
 template <typename R>
-__device__ __forceinline__ R frame_pick(uint32_t k, int f, R v0, R v1, R v2)
+__device__ __forceinline__ R frame_pick(Pivot k, int f, R v0, R v1, R v2)
 {
-    const uint32_t c = (k + (uint32_t)f) % 3u;
-    return c == 0 ? v0 : (c == 1 ? v1 : v2);
+    const R v[3] = {v0, v1, v2};
+    return k.k2 ? v[(2 + f) % 3] : (k.k1 ? v[(1 + f) % 3] : v[f]);
 }
 
 // natural column c of a row held in frame order (x0, x1, x2) = columns (k, k+1, k+2)
 template <typename R>
-__device__ __forceinline__ R natural_pick(uint32_t k, int c, R x0, R x1, R x2)
+__device__ __forceinline__ R natural_pick(Pivot k, int c, R x0, R x1, R x2)
 {
-    const uint32_t f = ((uint32_t)c + 3u - k) % 3u;
-    return f == 0 ? x0 : (f == 1 ? x1 : x2);
+    const R x[3] = {x0, x1, x2};
+    return k.k2 ? x[(c + 1) % 3] : (k.k1 ? x[(c + 2) % 3] : x[c]);
 }
 
 // The 8 stored values (flag bits k, q already taken out of their low bits,
 // which stay in the values: one unit in the last place) -> the link's 3x3
 // matrix, computed in R.
 template <typename R>
-__device__ __forceinline__ void decode_min8_vals(const R (&v)[8], uint32_t k, bool q, M3<R>& u)
+__device__ __forceinline__ void decode_min8_vals(const R (&v)[8], Pivot k, bool q, M3<R>& u)
 {
     const R air = v[0], aii = v[1], ajr = v[2], aji = v[3];
     const R t0 = v[4], sr = v[5], si = v[6], t1 = v[7];
@@ -295,14 +293,13 @@ __device__ __forceinline__ void decode_min8_vals(const R (&v)[8], uint32_t k, bo
 // Rows 0 and 1 of a link (orthonormal to rounding) -> the 8 values (without
 // flag bits), the pivot k and q, computed in R; tangents held to clamp.
 template <typename R>
-__device__ __forceinline__ void encode_min8_vals(const M3<R>& u, R clamp, R (&v)[8], uint32_t& kk, bool& qq)
+__device__ __forceinline__ void encode_min8_vals(const M3<R>& u, R clamp, R (&v)[8], Pivot& kk, bool& qq)
 {
     const R m0 = fmad(u.re[0][0], u.re[0][0], u.im[0][0] * u.im[0][0]);
     const R m1 = fmad(u.re[0][1], u.re[0][1], u.im[0][1] * u.im[0][1]);
     const R m2 = fmad(u.re[0][2], u.re[0][2], u.im[0][2] * u.im[0][2]);
-    uint32_t k = m1 > m0 ? 1u : 0u;
     const R mk = fmax(m0, m1);
-    if (m2 > mk) k = 2u;
+    const Pivot k{m1 > m0 && !(m2 > mk), m2 > mk};
     const R ak2 = fmax(mk, m2);
     const R akr = frame_pick(k, 0, u.re[0][0], u.re[0][1], u.re[0][2]);
     const R aki = frame_pick(k, 0, u.im[0][0], u.im[0][1], u.im[0][2]);
@@ -346,30 +343,30 @@ __device__ __forceinline__ void encode_min8_vals(const M3<R>& u, R clamp, R (&v)
 __device__ __forceinline__ void decode_min8(const double2 (&p)[kMin8Chunks], M3<double>& u)
 {
     const double v[8] = {p[0].x, p[0].y, p[1].x, p[1].y, p[2].x, p[2].y, p[3].x, p[3].y};
-    decode_min8_vals(v, low_bit(v[0]) | (low_bit(v[1]) << 1), low_bit(v[5]) != 0u, u);
+    decode_min8_vals(v, Pivot{low_bit(v[0]) != 0u, low_bit(v[1]) != 0u}, low_bit(v[5]) != 0u, u);
 }
 
 __device__ __forceinline__ void decode_min8(const float4 (&p)[kMin8Chunks32], M3<float>& u)
 {
     const float v[8] = {p[0].x, p[0].y, p[0].z, p[0].w, p[1].x, p[1].y, p[1].z, p[1].w};
-    decode_min8_vals(v, low_bit(v[0]) | (low_bit(v[1]) << 1), low_bit(v[5]) != 0u, u);
+    decode_min8_vals(v, Pivot{low_bit(v[0]) != 0u, low_bit(v[1]) != 0u}, low_bit(v[5]) != 0u, u);
 }
 
 // Float32 stored values decoded in float64.
 __device__ __forceinline__ void decode_min8(const float4 (&p)[kMin8Chunks32], M3<double>& u)
 {
     const double v[8] = {p[0].x, p[0].y, p[0].z, p[0].w, p[1].x, p[1].y, p[1].z, p[1].w};
-    decode_min8_vals(v, low_bit(p[0].x) | (low_bit(p[0].y) << 1), low_bit(p[1].y) != 0u, u);
+    decode_min8_vals(v, Pivot{low_bit(p[0].x) != 0u, low_bit(p[0].y) != 0u}, low_bit(p[1].y) != 0u, u);
 }
 
 // Rows 0 and 1 of a link (orthonormal to rounding) -> its stored chunks.
 __device__ __forceinline__ void encode_min8(const M3<double>& u, double2 (&p)[kMin8Chunks])
 {
     double v[8];
-    uint32_t k;
+    Pivot k;
     bool q;
     encode_min8_vals(u, tan_clamp<double>(), v, k, q);
-    p[0] = make_double2(with_low_bit(v[0], k & 1u), with_low_bit(v[1], k >> 1));
+    p[0] = make_double2(with_low_bit(v[0], k.k1 ? 1u : 0u), with_low_bit(v[1], k.k2 ? 1u : 0u));
     p[1] = make_double2(v[2], v[3]);
     p[2] = make_double2(v[4], with_low_bit(v[5], q ? 1u : 0u));
     p[3] = make_double2(v[6], v[7]);
@@ -379,11 +376,11 @@ template <typename R>
 __device__ __forceinline__ void encode_min8(const M3<R>& u, float4 (&p)[kMin8Chunks32])
 {
     R v[8];
-    uint32_t k;
+    Pivot k;
     bool q;
     encode_min8_vals(u, (R)tan_clamp<float>(), v, k, q);
-    p[0] = make_float4(with_low_bit((float)v[0], k & 1u), with_low_bit((float)v[1], k >> 1), (float)v[2],
-                       (float)v[3]);
+    p[0] = make_float4(with_low_bit((float)v[0], k.k1 ? 1u : 0u), with_low_bit((float)v[1], k.k2 ? 1u : 0u),
+                       (float)v[2], (float)v[3]);
     p[1] = make_float4((float)v[4], with_low_bit((float)v[5], q ? 1u : 0u), (float)v[6], (float)v[7]);
 }
 

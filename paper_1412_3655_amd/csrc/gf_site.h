@@ -66,15 +66,6 @@ __host__ __device__ __forceinline__ Rule<R> hb_rule(R T, uint32_t key0, uint32_t
     return Rule<R>{R(1), T, key0, key1, sweep, {}};
 }
 
-// 1/sqrt(x) to about one unit in the last place for normal x far from overflow:
-// the hardware seed and one third-order step.
-__device__ __forceinline__ double rsqrt_of(double x)
-{
-    const double y = __builtin_amdgcn_rsq(x);
-    const double e = fmad(-(x * y), y, 1.0);
-    return fmad(y * e, fmad(e, 0.375, 0.5), y);
-}
-
 // Squares below this leave the range of rsqrt_of.
 constexpr double kTinySquare = 0x1p-960;
 
