@@ -208,11 +208,15 @@ template <bool NT>
 __device__ __forceinline__ void st16(float4* p, float4 v)
 {
     if constexpr (NT) {
-        nt_v4f w;
-        w.x = v.x;
-        w.y = v.y;
-        w.z = v.z;
-        w.w = v.w;
+        // the empty statements hide from the optimiser that w interleaves two arrays
+        // of the caller: it would gather them as vectors from memory, and keep
+        // parts of every float32 12-real link in LDS and scratch for that
+        float x = v.x, y = v.y, z = v.z, t = v.w;
+        asm("" : "+v"(x));
+        asm("" : "+v"(y));
+        asm("" : "+v"(z));
+        asm("" : "+v"(t));
+        const nt_v4f w = {x, y, z, t};
         __builtin_nontemporal_store(w, (nt_v4f*)p);
     } else {
         *p = v;
