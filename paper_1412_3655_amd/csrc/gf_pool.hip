@@ -1348,7 +1348,11 @@ gf_status gf_pool_autotune(gf_pool P, int32_t kernel, int32_t n_sweeps, size_t s
     }
     int best_tps = 0, best_block = 0, best_cp = 0, m = 0;
     double best_us = 1e300;
-    for (int si = 0; si < kNShapes && st == GF_OK && e == hipSuccess; ++si) {
+    int order[kNShapes];  // fastest first
+    for (int si = 0; si < kNShapes; ++si) order[si] = si;
+    std::stable_sort(order, order + kNShapes, [&](int a, int b) { return shape_us[a] < shape_us[b]; });
+    for (int k = 0; k < kNShapes && st == GF_OK && e == hipSuccess; ++k) {
+        const int si = order[k];
         const int tps = shapes[si][0], block = shapes[si][1], cp = shapes[si][2];
         if (m < cap) table[m] = gf_tune_entry{tps, block, cp, 0, shape_us[si]};
         ++m;
