@@ -204,14 +204,15 @@ gf_status gf_lattice_info(gf_lattice lat, int64_t* volume, int64_t* device_bytes
  * and the register limit (min_waves: 0 = the compiler's allocation, 2 = at
  * least 2 waves per SIMD, at most 256 registers per lane; 2 only with tps 1,
  * and it changes only float64 kernels, the paper's register-limit axis of
- * Sec. 5).  Every valid choice gives bitwise the same links.  Default
- * 4 / 256 / 0 / 0. */
+ * Sec. 5).  Every valid choice gives bitwise the same links.  Default:
+ * chosen from the lattice's size, precision and storage (more lanes and small
+ * blocks for few sites, non-temporal accesses while the links fit the L2s). */
 gf_status gf_set_sweep_config(gf_lattice lat, gf_prec kernel, int32_t tps, int32_t block, int32_t nontemporal,
                               int32_t min_waves);
 
 /* The same for the heat-bath sweeps of gf_anneal, which sample every
  * subgroup element in each lane of a site's group (so fewer lanes do less
- * arithmetic).  Default 1 / 256 / 0 for float32, 1 / 128 / 2 for float64. */
+ * arithmetic); the default is chosen in the same way. */
 gf_status gf_set_anneal_config(gf_lattice lat, gf_prec kernel, int32_t tps, int32_t block, int32_t nontemporal,
                                int32_t min_waves);
 
@@ -556,8 +557,8 @@ gf_status gf_pool_cancel(gf_pool pool, uint64_t job_id);
  * colours) of that set for every shape (lanes per site 1, 2, 4; threads per
  * block 64, 128, 256; cache policy plain or non-temporal: 18 shapes) with HIP
  * events, in two rounds over all shapes of which each shape keeps its faster
- * time, writes up to cap entries to table (may be NULL; nontemporal = 0 plain,
- * 1 non-temporal), and makes the fastest the pool's shape and cache policy for
+ * time, writes up to cap entries to table, fastest first (may be NULL;
+ * nontemporal = 0 plain, 1 non-temporal), and makes the fastest the pool's shape and cache policy for
  * that kernel (*chosen, may be NULL).
  * The jobs' links are not changed.  GF_E_STATE if no resident job fits in
  * scratch_bytes.  Allocates and frees the copies.  Syncs. */

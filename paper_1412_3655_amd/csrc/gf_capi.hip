@@ -164,10 +164,30 @@ gf_status check_omega(double omega, int mode)
     return GF_OK;
 }
 
+void apply_config(gf_lattice L, gf_prec kernel, bool heat_bath, const SweepConfig& c)
+{
+    if (heat_bath) {
+        (kernel == GF_FP32 ? L->cfg_hb32 : L->cfg_hb64) = c;
+        (kernel == GF_FP32 ? L->set_hb32 : L->set_hb64) = true;
+    } else {
+        (kernel == GF_FP32 ? L->cfg32 : L->cfg64) = c;
+        (kernel == GF_FP32 ? L->set32 : L->set64) = true;
+    }
+}
+
 const OrOmega& or_omega(gf_lattice L, double omega)
 {
     if (L->om.omega != omega) L->om = make_or_omega(omega);
     return L->om;
+}
+
+void default_configs(gf_lattice L)
+{
+    const int r64 = L->group == 2 ? 4 : (min8_64(L) ? 8 : 12), r32 = L->group == 2 ? 4 : (L->min8 ? 8 : 12);
+    if (!L->set64) L->cfg64 = gf::default_sweep_config(L->geom, true, r64, false);
+    if (!L->set32) L->cfg32 = gf::default_sweep_config(L->geom, false, r32, false);
+    if (!L->set_hb64) L->cfg_hb64 = gf::default_sweep_config(L->geom, true, r64, true);
+    if (!L->set_hb32) L->cfg_hb32 = gf::default_sweep_config(L->geom, false, r32, true);
 }
 
 gf_status do_half_sweep(gf_lattice L, int parity, double omega, int mode)
@@ -516,6 +536,7 @@ gf_status do_set_storage(gf_lattice L, bool min8)
         L->bytes += (int64_t)to.f32 - (int64_t)from.f32;
     }
     L->min8 = min8;
+    default_configs(L);
     clear_graphs(L);  // captured launches hold the old field's address
     return GF_OK;
 }
@@ -612,20 +633,7 @@ gf_status create_lattice(const int32_t dims[4], gf_prec prec, int group, bool mi
         return fail(e == hipErrorOutOfMemory ? GF_E_NOMEM : GF_E_HIP, "allocation failed: %s", hipGetErrorString(e));
     }
     L->bytes = z.total;
-    L->cfg64 = SweepConfig{4, 256};
-    L->cfg32 = SweepConfig{4, 256};
-    // The heat bath samples each subgroup element in every lane of a site's
-    // group, so its arithmetic grows with the lanes per site: one lane is the
-    // fastest shape on MI355X (32^4: float32 with g 175 us per sweep at 1 lane
-    // vs 282 us at 4; float64 414 us vs 544 us at 2).
-    L->cfg_hb64 = SweepConfig{1, 128, 2};
-    L->cfg_hb32 = SweepConfig{1, 256, 0};
-    if (group == 2) {
-        // one lane per site: the SU(2) site update is a few quaternion products
-        L->cfg64 = SweepConfig{1, 256, 0};
-        L->cfg32 = SweepConfig{1, 256, 0};
-        L->cfg_hb64 = SweepConfig{1, 256, 0};
-    }
+    default_configs(L);
     *out = L;
     return GF_OK;
 }
@@ -712,10 +720,7 @@ gf_status set_config(gf_lattice L, gf_prec kernel, int32_t tps, int32_t block, i
                     tps, block, nontemporal, min_waves);
     if ((kernel == GF_FP64 ? min8_64(L) : L->min8) && min_waves != 0)
         return fail(GF_E_ARG, "8-real links: min_waves must be 0 (the register cap is an axis of the 12-real kernel)");
-    if (heat_bath)
-        (kernel == GF_FP32 ? L->cfg_hb32 : L->cfg_hb64) = c;
-    else
-        (kernel == GF_FP32 ? L->cfg32 : L->cfg64) = c;
+    apply_config(L, kernel, heat_bath, c);
     return GF_OK;
 }
 

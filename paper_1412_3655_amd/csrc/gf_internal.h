@@ -45,6 +45,9 @@ struct gf_lattice_ {
     gf::SweepConfig cfg32;
     gf::SweepConfig cfg_hb64;  // heat-bath sweeps (gf_anneal)
     gf::SweepConfig cfg_hb32;
+    // whether cfg64, cfg32, cfg_hb64, cfg_hb32 were set by the caller or a tuner;
+    // the others follow default_sweep_config (default_configs)
+    bool set64 = false, set32 = false, set_hb64 = false, set_hb32 = false;
     // hipGraphs of n back-to-back sweeps, keyed by (n, omega, mode, precision
     // and g tracking plus 4 x gauge, tps, block, cache policy); only on a
     // non-default stream
@@ -106,6 +109,10 @@ gf_status check_omega(double omega, int mode);
 // The lattice's OrOmega, made anew when omega is not that of its last sweeps (a
 // few microseconds, once per call of an entry point).
 const OrOmega& or_omega(gf_lattice L, double omega);
+// Set a configuration for the caller or a tuner.
+void apply_config(gf_lattice L, gf_prec kernel, bool heat_bath, const SweepConfig& c);
+// Configurations that nobody set, for the lattice's size and storage.
+void default_configs(gf_lattice L);
 gf_status do_half_sweep(gf_lattice L, int parity, double omega, int mode);
 gf_status do_sweeps(gf_lattice L, int32_t n, double omega, int mode);
 gf_status do_reunitarize(gf_lattice L);

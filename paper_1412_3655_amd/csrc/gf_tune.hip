@@ -90,14 +90,10 @@ gf_status tune(gf_lattice L, gf_prec kernel, bool heat_bath, int32_t n_sweeps, c
         return fail(GF_E_STATE, "the storage of links can change for SU(3) links of the sweeping precision only");
     const bool cur8 = kernel == GF_FP64 ? min8_64(L) : L->min8;  // storage of the kernel's links
     const bool m8 = cur8 != other_storage;                       // storage of the links timed
-    SweepConfig scratch_target{};
-    SweepConfig& target = other_storage ? scratch_target
-                                        : heat_bath ? (kernel == GF_FP32 ? L->cfg_hb32 : L->cfg_hb64)
-                                                    : (kernel == GF_FP32 ? L->cfg32 : L->cfg64);
     const std::string key = cache_key(L, kernel, m8) + (heat_bath ? "-hb" : "");
     SweepConfig best{};
     if (cache_path && cache_lookup(cache_path, key, &best)) {
-        target = best;
+        if (!other_storage) apply_config(L, kernel, heat_bath, best);
         if (chosen) *chosen = gf_tune_entry{best.tps, best.block, best.nt, best.minw, 0.0};
         return GF_OK;
     }
@@ -223,7 +219,7 @@ gf_status tune(gf_lattice L, gf_prec kernel, bool heat_bath, int32_t n_sweeps, c
     if (scratch) (void)hipFree(scratch);
     if (gscratch) (void)hipFree(gscratch);
     if (st != GF_OK) return st;
-    target = best;
+    if (!other_storage) apply_config(L, kernel, heat_bath, best);
     if (n_out) *n_out = std::min(n, cap);
     if (chosen) *chosen = gf_tune_entry{best.tps, best.block, best.nt, best.minw, best_us};
     if (cache_path) {
@@ -261,7 +257,7 @@ extern "C" gf_status gf_autotune_storage(gf_lattice L, int32_t n_sweeps, int32_t
     if (us_8) *us_8 = L->min8 ? t_cur : t_oth;
     if (t_oth < t_cur) {
         GF_TRY(do_set_storage(L, !L->min8));
-        (kernel == GF_FP64 ? L->cfg64 : L->cfg32) = SweepConfig{oth.tps, oth.block, oth.nontemporal, oth.min_waves};
+        apply_config(L, kernel, false, SweepConfig{oth.tps, oth.block, oth.nontemporal, oth.min_waves});
     }
     if (reals_per_link) *reals_per_link = L->min8 ? 8 : 12;
     return GF_OK;
