@@ -366,7 +366,7 @@ __global__ void __launch_bounds__(RBLOCK) k_unpack(Field f, Geom g, double* cano
     canon2* out = (canon2*)(canon + (size_t)done * 72);
     for (uint32_t q = threadIdx.x; q < left * 36; q += RBLOCK) {
         const double2 v = ((const double2*)rows)[q / 36 * (kCanonRow / 2) + q % 36];
-        out[q] = canon2{v.x, v.y};
+        __builtin_nontemporal_store(canon2{v.x, v.y}, out + q);
     }
 }
 

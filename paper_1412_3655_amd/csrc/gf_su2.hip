@@ -278,7 +278,7 @@ __global__ void __launch_bounds__(RB) k_su2_unpack(Su2Field<R> f, Geom g, double
     canon2* out = (canon2*)(canon + (size_t)done * 32);
     for (uint32_t k = threadIdx.x; k < left * 16; k += RB) {
         const double2 v = ((const double2*)row)[k / 16 * (kUnpackRow / 2) + k % 16];
-        out[k] = canon2{v.x, v.y};
+        __builtin_nontemporal_store(canon2{v.x, v.y}, out + k);
     }
 }
 
