@@ -266,9 +266,22 @@ def gf_last_error() -> str:
     return lib().gf_last_error().decode(errors="replace")
 
 
-# hip stream handle of each live lattice (None = the default stream), so that the
-# device-array calls can order the lattice's stream against torch's
-_LATTICE_STREAM = {}
+class _Record:
+    """What the binding keeps of a live lattice: its hip stream handle (None = the default
+    stream), so that the device-array calls can order that stream against torch's, with the
+    torch stream and the two events they do it with (an event may be recorded again once the
+    wait on it is enqueued), and its canonical array's size.  A wait_stream per call, which makes
+    a stream object and an event each time, cost 25 us of host time in gf_set_links and 34 us in
+    gf_get_links, as much as the GPU needs for 10 half-sweeps of 8^4."""
+
+    __slots__ = ("handle", "volume", "per_site", "device", "stream", "before", "after")
+
+    def __init__(self, handle, volume, per_site):
+        self.handle, self.volume, self.per_site = handle, volume, per_site
+        self.device = self.stream = self.before = self.after = None
+
+
+_LATTICES = {}
 
 
 def gf_create_lattice(dims, prec: int = GF_FP64, stream=None, group: int = 3, storage: int = 12) -> ctypes.c_void_p:
@@ -292,7 +305,8 @@ def gf_create_lattice(dims, prec: int = GF_FP64, stream=None, group: int = 3, st
                 err = GFError(st, lib().gf_last_error().decode(errors="replace"))
                 lib().gf_destroy_lattice(out)
                 raise err
-    _LATTICE_STREAM[out.value] = h
+    nc = 2 if group == 2 else 3
+    _LATTICES[out.value] = _Record(h, d[0] * d[1] * d[2] * d[3], 8 * nc * nc)
     return out
 
 
@@ -325,40 +339,61 @@ def gf_lattice_group(lat) -> int:
 
 def gf_destroy_lattice(lat) -> None:
     _call("gf_destroy_lattice", lat)
-    _LATTICE_STREAM.pop(getattr(lat, "value", lat), None)
+    _LATTICES.pop(getattr(lat, "value", lat), None)
 
 
-def _lattice_stream(lat, tensor):
+def _record(lat) -> _Record:
+    """The lattice's record (made for the call, on the default stream, for a handle that did not
+    come from this module's gf_create_lattice)."""
+    key = getattr(lat, "value", lat)
+    r = _LATTICES.get(key)
+    if r is None:
+        volume, _ = gf_lattice_info(lat)
+        nc = gf_lattice_group(lat)
+        r = _Record(None, volume, 8 * nc * nc)
+    return r
+
+
+def _streams(r: _Record, tensor):
     """(torch's current stream on the tensor's device, the lattice's stream as a torch
     stream), or None when the two are the same stream."""
     import torch
 
-    cur = torch.cuda.current_stream(tensor.device)
-    h = _LATTICE_STREAM.get(getattr(lat, "value", lat))
-    if (h or 0) == int(cur.cuda_stream):
+    dev = tensor.device
+    cur = torch.cuda.current_stream(dev)
+    if (r.handle or 0) == int(cur.cuda_stream):
         return None
-    ls = torch.cuda.ExternalStream(h, device=tensor.device) if h else torch.cuda.default_stream(tensor.device)
-    return cur, ls
+    if r.device != dev:
+        r.device = dev
+        r.stream = torch.cuda.ExternalStream(r.handle, device=dev) if r.handle else torch.cuda.default_stream(dev)
+        r.before, r.after = torch.cuda.Event(), torch.cuda.Event()
+    return cur, r.stream
 
 
-def _before_lattice_reads(lat, tensor) -> None:
+def _before_lattice_reads(r: _Record, tensor) -> None:
     """The lattice's stream waits for torch's current stream (which produced the
-    tensor), and the caching allocator keeps the tensor's memory until the lattice's
-    stream has used it."""
-    pair = _lattice_stream(lat, tensor)
+    tensor) unless that has nothing left to do (a wait between two queues holds the
+    GPU up for some 10 us; a capturing stream cannot be asked), and the caching
+    allocator keeps the tensor's memory until the lattice's stream has used it."""
+    import torch
+
+    pair = _streams(r, tensor)
     if pair is not None:
         cur, ls = pair
-        ls.wait_stream(cur)
+        if torch.cuda.is_current_stream_capturing() or not cur.query():
+            r.before.record(cur)
+            ls.wait_event(r.before)
         tensor.record_stream(ls)
 
 
-def _after_lattice_writes(lat, tensor) -> None:
+def _after_lattice_writes(r: _Record, tensor) -> None:
     """Torch's current stream waits for the lattice's stream (which wrote the tensor)."""
-    pair = _lattice_stream(lat, tensor)
+    pair = _streams(r, tensor)
     if pair is not None:
         cur, ls = pair
         tensor.record_stream(ls)
-        cur.wait_stream(ls)
+        r.after.record(ls)
+        cur.wait_event(r.after)
 
 
 def gf_lattice_info(lat):
@@ -414,15 +449,13 @@ def gf_promote_fp64(lat) -> None:
 
 
 def gf_set_links(lat, links) -> None:
-    volume, _ = gf_lattice_info(lat)
-    nc = gf_lattice_group(lat)
-    per_site = 4 * 2 * nc * nc
+    r = _record(lat)
     if _is_device_tensor(links):
-        t = _device_links(links, volume, per_site)
-        _before_lattice_reads(lat, t)
+        t = _device_links(links, r.volume, r.per_site)
+        _before_lattice_reads(r, t)
         _call("gf_set_links_device", lat, t.data_ptr())
     else:
-        u = _host_links(links, volume, per_site)
+        u = _host_links(links, r.volume, r.per_site)
         _call("gf_set_links", lat, u.ctypes.data_as(_dp))
 
 
@@ -432,18 +465,17 @@ def gf_set_links_device(lat, dev_ptr: int) -> None:
 
 def gf_get_links(lat, out=None):
     """Links as a canonical array: into `out` (numpy or device tensor) or a new numpy array."""
-    volume, _ = gf_lattice_info(lat)
-    nc = gf_lattice_group(lat)
-    per_site = 4 * 2 * nc * nc
+    r = _record(lat)
     if out is None:
-        out = np.empty((volume, 4, nc, nc, 2), dtype=np.float64)
+        nc = 2 if r.per_site == 32 else 3
+        out = np.empty((r.volume, 4, nc, nc, 2), dtype=np.float64)
     if _is_device_tensor(out):
-        t = _device_links(out, volume, per_site)
-        _before_lattice_reads(lat, t)  # earlier torch work on `out` completes first
+        t = _device_links(out, r.volume, r.per_site)
+        _before_lattice_reads(r, t)  # earlier torch work on `out` completes first
         _call("gf_get_links_device", lat, t.data_ptr())
-        _after_lattice_writes(lat, t)
+        _after_lattice_writes(r, t)
     else:
-        u = _host_links(out, volume, per_site)
+        u = _host_links(out, r.volume, r.per_site)
         _call("gf_get_links", lat, u.ctypes.data_as(_dp))
     return out
 

@@ -67,3 +67,27 @@ def test_pool_moves_a_lattice_in_chunks(reals):
         assert [d["job_id"] for d in pool.poll()] == [1]
         got = pool.fetch_links(1)
     assert np.abs(got - u).max() <= 1e-14
+
+
+@pytest.mark.parametrize("busy", [False, True])
+def test_device_arrays_are_ordered_after_torch(busy):
+    """A lattice on its own stream takes links that torch's current stream has yet to produce
+    (busy: behind 10 ms of waiting) and fills an array that torch has yet to write, twice over."""
+    dims = (6, 4, 4, 6)
+    links = [gi.gen_links(dims, 0.8, k) for k in (31, 32)]
+    out = torch.empty(links[0].shape, dtype=torch.float64, device="cuda")
+    with gf.Lattice(dims, stream=torch.cuda.Stream()) as lat:
+        for u in links:
+            src = torch.from_numpy(u).cuda()
+            torch.cuda.synchronize()
+            if busy:
+                torch.cuda._sleep(20_000_000)
+            tmp = src * 1.0
+            lat.set_links(tmp)
+            del tmp
+            if busy:
+                torch.cuda._sleep(20_000_000)
+                out.fill_(float("nan"))
+            lat.get_links(out)
+            got = (out * 1.0).cpu().numpy()
+            assert np.array_equal(got[:, :, :2], u[:, :, :2])
