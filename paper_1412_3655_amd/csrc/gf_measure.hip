@@ -14,6 +14,8 @@
 // reduction order depends only on the lattice shape, so results are bitwise
 // reproducible.  Traffic: every link is read twice (once from each end),
 // 768 B per site in FP64.
+#include <algorithm>
+
 #include "gf_kernels.h"
 #include "gf_site.h"
 
@@ -63,9 +65,44 @@ __global__ void __launch_bounds__(RBLOCK) k_finalize_slices(const double* partia
     finalize_pairs<RBLOCK>(partial + 2 * (size_t)blockIdx.x * n, n, s0, s1, out + 2 * (size_t)blockIdx.x);
 }
 
-// Re tr[U_mu(x) U_nu(x+mu^) U_mu(x+nu^)^dag U_nu(x)^dag] summed over mu < nu.
-// The 12 matrix products of a site bound it (2035 vector instructions, 2 waves
-// per SIMD): with explicit multiply-adds 172 -> 150 us on 32^4 float64.
+// Re tr[a b c^dag d^dag]: with P = a b and Q = d c, sum_ij P_ij conj(Q_ij).
+__device__ __forceinline__ double loop_trace(const M3<double>& a, const M3<double>& b, const M3<double>& c,
+                                             const M3<double>& d)
+{
+    double re = 0.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            double pr = 0.0, pi = 0.0, qr = 0.0, qi = 0.0;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                pr = fmad(a.re[i][k], b.re[k][j], fmad(-a.im[i][k], b.im[k][j], pr));
+                pi = fmad(a.re[i][k], b.im[k][j], fmad(a.im[i][k], b.re[k][j], pi));
+                qr = fmad(d.re[i][k], c.re[k][j], fmad(-d.im[i][k], c.im[k][j], qr));
+                qi = fmad(d.re[i][k], c.im[k][j], fmad(d.im[i][k], c.re[k][j], qi));
+            }
+            re = fmad(pr, qr, fmad(pi, qi, re));
+        }
+    return re;
+}
+
+// Re tr[U_mu(x) U_nu(x+mu^) U_mu(x+nu^)^dag U_nu(x)^dag] at the site (parity, h).
+template <typename Field>
+__device__ __forceinline__ double plane_trace(const Field& f, const Geom& g, const Site& s, int parity, uint32_t h,
+                                              int mu, int nu)
+{
+    M3<double> a, b, c, d;
+    load_full_f64(f, parity, mu, h, a);
+    load_full_f64(f, 1 - parity, nu, fwd_h(g, h, s, mu), b);
+    load_full_f64(f, 1 - parity, mu, fwd_h(g, h, s, nu), c);
+    load_full_f64(f, parity, nu, h, d);
+    return loop_trace(a, b, c, d);
+}
+
+// The plaquettes summed over mu < nu, a thread per site.  The 12 matrix products
+// of a site bound it (2035 vector instructions, 2 wavefronts per SIMD): with
+// explicit multiply-adds 172 -> 150 us on 32^4 float64.
 template <typename Field>
 __global__ void __launch_bounds__(RBLOCK) k_plaquette(Field f, Geom g, double* partial)
 {
@@ -79,32 +116,68 @@ __global__ void __launch_bounds__(RBLOCK) k_plaquette(Field f, Geom g, double* p
 #pragma unroll
         for (int mu = 0; mu < 4; ++mu)
 #pragma unroll
-            for (int nu = mu + 1; nu < 4; ++nu) {
-                M3<double> a, b, c, d;
-                load_full_f64(f, parity, mu, h, a);
-                load_full_f64(f, 1 - parity, nu, fwd_h(g, h, s, mu), b);
-                load_full_f64(f, 1 - parity, mu, fwd_h(g, h, s, nu), c);
-                load_full_f64(f, parity, nu, h, d);
-                // P = a b, Q = d c; tr[P Q^dag] = sum_ij P_ij conj(Q_ij)
-                double re = 0.0;
-#pragma unroll
-                for (int i = 0; i < 3; ++i)
-#pragma unroll
-                    for (int j = 0; j < 3; ++j) {
-                        double pr = 0.0, pi = 0.0, qr = 0.0, qi = 0.0;
-#pragma unroll
-                        for (int k = 0; k < 3; ++k) {
-                            pr = fmad(a.re[i][k], b.re[k][j], fmad(-a.im[i][k], b.im[k][j], pr));
-                            pi = fmad(a.re[i][k], b.im[k][j], fmad(a.im[i][k], b.re[k][j], pi));
-                            qr = fmad(d.re[i][k], c.re[k][j], fmad(-d.im[i][k], c.im[k][j], qr));
-                            qi = fmad(d.re[i][k], c.im[k][j], fmad(d.im[i][k], c.re[k][j], qi));
-                        }
-                        re = fmad(pr, qr, fmad(pi, qi, re));
-                    }
-                acc += re;
-            }
+            for (int nu = mu + 1; nu < 4; ++nu) acc += plane_trace(f, g, s, parity, h, mu, nu);
     }
     block_sum2<RBLOCK>(acc, 0.0, partial + 2 * (size_t)(parity * tiles + tile));
+}
+
+// Sites of one colour a block of k_plaquette_halves takes, and the bytes of links
+// (both colours, one timeslice) that a column of its tiles spans.
+constexpr uint32_t HALF_SITES = RBLOCK / 2;
+constexpr uint32_t PLAQ_COLUMN_BYTES = 2304 * 1024;
+
+// The tile at place q of T in column order: the tiles are rows of `row` (one
+// timeslice, rounded down to whole tiles), cut into columns of `col`; a column
+// is walked through all rows before the next one, and what is left over after
+// the whole rows comes last.  A permutation of 0..T-1.
+__device__ __forceinline__ uint32_t column_tile(uint32_t q, uint32_t T, uint32_t row, uint32_t col)
+{
+    const uint32_t rows = T / row;
+    if (q >= rows * row) return q;
+    const uint32_t c = q / (col * rows);
+    const uint32_t r = q - c * col * rows;
+    const uint32_t left = row - c * col;
+    const uint32_t w = col < left ? col : left;
+    const uint32_t t = r / w;
+    return t * row + c * col + (r - t * w);
+}
+
+// The same by two threads per site: the first two wavefronts of a block take the
+// planes (0, nu), the others the remaining three.  All 16 links and 6 planes in
+// one thread leave 2 wavefronts per SIMD too few loads in flight; halves, though
+// they load 19 links, hide them better.  The links at x + t^ are a timeslice
+// away, more than an XCD's L2 holds on a large lattice, so tiles go in columns
+// whose timeslice is about half an L2.  float64, 12 reals: 32^4 141 -> 122 us by
+// the halves, -> 118 by the columns (every link once at the rate of a large copy:
+// 80); 48^3x96 1501 -> 1412 -> 1236; float32 920 -> 884 -> 832; 8^4 7.4 -> 5.7.
+// partial holds, per tile, the sums of colour 0 and colour 1.
+template <typename Field>
+__global__ void __launch_bounds__(RBLOCK) k_plaquette_halves(Field f, Geom g, uint32_t row, uint32_t col,
+                                                             double* partial)
+{
+    const uint32_t b = xcd_block(blockIdx.x, gridDim.x);
+    const int parity = (int)(b & 1u);
+    const uint32_t tile = column_tile(b >> 1, gridDim.x >> 1, row, col);
+    const uint32_t h = tile * HALF_SITES + threadIdx.x % HALF_SITES;
+    double acc = 0.0;
+    if (h < g.vh) {
+        const Site s = decode_site(g, parity, h);
+        if (threadIdx.x < HALF_SITES)
+            acc = plane_trace(f, g, s, parity, h, 0, 1) + plane_trace(f, g, s, parity, h, 0, 2) +
+                  plane_trace(f, g, s, parity, h, 0, 3);
+        else
+            acc = plane_trace(f, g, s, parity, h, 1, 2) + plane_trace(f, g, s, parity, h, 1, 3) +
+                  plane_trace(f, g, s, parity, h, 2, 3);
+    }
+    __shared__ double lds[RBLOCK / 64];
+    acc = wave_sum(acc);
+    if (threadIdx.x % 64 == 0) lds[threadIdx.x / 64] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double sum = 0.0;
+        for (int i = 0; i < RBLOCK / 64; ++i) sum += lds[i];
+        partial[2 * (size_t)tile + parity] = sum;
+    }
 }
 
 // The nine independent real components of Delta = [(K - K^dag)/(2i)]_traceless:
@@ -214,6 +287,14 @@ __global__ void __launch_bounds__(RBLOCK) k_fp32_floor(LinkField<double> f, Geom
 __global__ void __launch_bounds__(RBLOCK) k_finalize(const double* partial, uint32_t n, double s0, double s1, double* out)
 {
     finalize_pairs<RBLOCK>(partial, n, s0, s1, out);
+}
+
+// out[0] = scale * sum of all 2 n partials, the two of a pair kept apart till last.
+__global__ void __launch_bounds__(RBLOCK) k_finalize_halves(const double* partial, uint32_t n, double scale, double* out)
+{
+    __shared__ double sums[2];
+    finalize_pairs<RBLOCK>(partial, n, scale, scale, sums);
+    if (threadIdx.x == 0) out[0] = sums[0] + sums[1];
 }
 
 // Gram-Schmidt on rows 0, 1 (row 2 stays implicit).
@@ -416,13 +497,40 @@ hipError_t measure_slices_impl(const Field& f, const Geom& g, double* partial, d
     return hipGetLastError();
 }
 
+template <typename R>
+constexpr uint32_t site_bytes(const LinkField<R>&)
+{
+    return 4 * 12 * sizeof(R);
+}
+
+template <typename F>
+constexpr uint32_t site_bytes(const F&)
+{
+    return 4 * 8 * sizeof(typename Min8Of<F>::R);
+}
+
 template <typename Field>
 hipError_t plaquette_impl(const Field& f, const Geom& g, double* partial, double* out, hipStream_t st)
 {
-    const uint32_t nb = site_blocks(g);
-    hipLaunchKernelGGL((k_plaquette<Field>), dim3(2 * nb), dim3(RBLOCK), 0, st, f, g, partial);
     const double V = 2.0 * (double)g.vh;
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(RBLOCK), 0, st, partial, 2 * nb, 1.0 / (18.0 * V), 0.0, out);
+    const double scale = 1.0 / (18.0 * V);
+    // Halves while the lattice fills 256 CUs at most once, 4 wavefronts each
+    // (12^4 float64 7.6 -> 5.9 us, of 8 reals 12.4 -> 8.5); then whole sites until
+    // those fill them once too (14^4 7.7, halved in two passes 8.8).  Beyond that
+    // 12 reals halve, while 8 reals pay for the three more links in decoding
+    // (32^4 float64 158 whole, 165 halved; 48^3x96 1667, 1684).
+    const uint32_t once = 256 * HALF_SITES, sites = 2 * g.vh;
+    if (sites <= once || (!Min8Of<Field>::value && sites > 2 * once)) {
+        const uint32_t tiles = (g.vh + HALF_SITES - 1) / HALF_SITES;  // pairs: at most measure_blocks
+        const uint32_t row = std::max(1u, g.hs3 / HALF_SITES);
+        const uint32_t col = std::min(row, PLAQ_COLUMN_BYTES / (2 * HALF_SITES * site_bytes(f)));
+        hipLaunchKernelGGL((k_plaquette_halves<Field>), dim3(2 * tiles), dim3(RBLOCK), 0, st, f, g, row, col, partial);
+        hipLaunchKernelGGL(k_finalize_halves, dim3(1), dim3(RBLOCK), 0, st, partial, tiles, scale, out);
+    } else {
+        const uint32_t nb = site_blocks(g);
+        hipLaunchKernelGGL((k_plaquette<Field>), dim3(2 * nb), dim3(RBLOCK), 0, st, f, g, partial);
+        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(RBLOCK), 0, st, partial, 2 * nb, scale, 0.0, out);
+    }
     return hipGetLastError();
 }
 

@@ -31,6 +31,24 @@ def test_landau_and_plaquette(dims):
     assert abs(got_F - F) <= tol and abs(got_P - P) <= tol
 
 
+# a thread or two per site, in columns of tiles: halves below 32768 sites, whole below 65536, then halves of
+# 12 reals: one column, two of 24 and 16 tiles whose timeslices are no whole number of tiles (float64), and
+# three tiles left over; 8 reals whole
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("reals", [12, 8])
+@pytest.mark.parametrize("dims", [(16, 16, 16, 8), (18, 16, 16, 8), (16, 16, 16, 18), (26, 22, 18, 10)])
+def test_plaquette_tiles(dims, prec, reals):
+    u = gi.gen_links(dims, 0.7, 6)
+    with gf.Lattice(dims, gf.GF_FP32 if prec == "f32" else gf.GF_FP64, storage=reals) as lat:
+        lat.set_links(u)
+        want = oracle.plaquette(lat.get_links(), dims)
+        got = lat.plaquette()
+    # as above; float32 storage may round row 2 on the way out: a trace / 3 of four links, each within 2^-23
+    tol = 8 * 2.0**-53 * np.sqrt(gi.volume(dims)) + 1e-15 if prec == "f64" else 4 * 2.0**-23
+    # the 8-real decode, relative 1e-15 per entry on average, much less over the lattice
+    assert abs(got - want) <= tol + (1e-13 if reals == 8 else 0.0)
+
+
 @pytest.mark.parametrize("dims", [(4, 6, 2, 10), (14, 10, 10, 6), (24, 24, 24, 2)])
 def test_coulomb_slices(dims):
     u = gi.gen_links(dims, 0.7, 4)
