@@ -123,10 +123,10 @@ __device__ __forceinline__ constexpr R tan_clamp()
 // correction); the float32 seeds are good to 2^-23.3, and the residual
 // correction alone rounds the square root correctly (a refinement step before it
 // gave the same bits over 2e6 values).  The sweeps of 8-real links are bound by
-// their vector instructions: with these steps, picks on two masks and an integer
-// flag a float32 wave at one lane per site went from 3966 to 3798 of them, a
-// float64 one at two lanes from 2702 to 2635 (32^4 float32 at 4 lanes 150 -> 127
-// us per sweep, 24^3x48 float64 136 -> 129).
+// their vector instructions: with these steps, an integer flag and picks of named
+// values on two masks a float32 wave at one lane per site went from 3966 to 3614
+// of them, a float64 one at two lanes from 2702 to 2466 (32^4 float32 at 4 lanes
+// 143 -> 134 us per sweep, 24^3x48 float64 at two 136 -> 126).
 
 // 1/d for 1 <= |d| < 2^1000
 __device__ __forceinline__ double recip(double d)
@@ -225,21 +225,33 @@ struct Pivot {
     bool k1, k2;
 };
 
-// v[c] for c = (k + f) mod 3, i.e. the entry of frame index f of a row whose
-// pivot column is k
+// Of three values at places 0, 1, 2, the one at place (f + pivot) mod 3.  The
+// operands are named, not indexed: from an array the compiler makes one lookup
+// by a computed place, and computes and compares that place for every pick (3798
+// instead of 3614 vector instructions of a float32 wave).
+template <typename R>
+__device__ __forceinline__ R pick(Pivot k, int f, R v0, R v1, R v2)
+{
+    const R zero = f == 0 ? v0 : (f == 1 ? v1 : v2);
+    const R one = f == 0 ? v1 : (f == 1 ? v2 : v0);
+    const R two = f == 0 ? v2 : (f == 1 ? v0 : v1);
+    const R low = k.k1 ? one : zero;
+    return k.k2 ? two : low;
+}
+
+// The entry of frame index f of a row whose pivot column is k
 template <typename R>
 __device__ __forceinline__ R frame_pick(Pivot k, int f, R v0, R v1, R v2)
 {
-    const R v[3] = {v0, v1, v2};
-    return k.k2 ? v[(2 + f) % 3] : (k.k1 ? v[(1 + f) % 3] : v[f]);
+    return pick(k, f, v0, v1, v2);
 }
 
-// natural column c of a row held in frame order (x0, x1, x2) = columns (k, k+1, k+2)
+// natural column c of a row held in frame order (x0, x1, x2) = columns (k, k+1,
+// k+2): its place is (c - k) mod 3, and (-c + k) mod 3 counted from the other end
 template <typename R>
 __device__ __forceinline__ R natural_pick(Pivot k, int c, R x0, R x1, R x2)
 {
-    const R x[3] = {x0, x1, x2};
-    return k.k2 ? x[(c + 1) % 3] : (k.k1 ? x[(c + 2) % 3] : x[c]);
+    return pick(k, (3 - c) % 3, x0, x2, x1);
 }
 
 // The 8 stored values (flag bits k, q already taken out of their low bits,
