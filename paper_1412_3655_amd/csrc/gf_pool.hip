@@ -16,9 +16,9 @@
 // its list's tile count (hipGraphExecKernelNodeSetParams).  The other kinds
 // (reunitarisation, measurement, finalisation) keep persistent grids that
 // stride over their tiles.  A persistent sweep was measured ~13 % slower on
-// MI355X: across the loop the compiler keeps the math library's polynomial
-// coefficients of the exact power in registers, which pushes the float64
-// sweep over the register file into accumulation-register spills.
+// MI355X: across the loop the compiler kept the coefficients of the exact power
+// (then the math library's) in vector registers, which pushed the float64 sweep
+// over the register file into accumulation-register spills.
 //
 // A step may be left running while the host admits, polls, fetches and
 // releases jobs (gf_pool_step_async): those touch only lattices that the step
@@ -49,12 +49,12 @@ constexpr int PBLOCK = 256;  // threads per block of the reunitarisation / measu
 constexpr int kHeatBathTps = 1;  // lanes per site of the heat-bath sweeps (its sampling is per lane)
 constexpr int kHeatBathBlock = 128;  // threads per block of the heat-bath sweeps
 // Default shape of the overrelaxation sweeps (lanes per site, threads per
-// block): the fastest over 64 lattices of 12^4 to 24^3x48 on MI355X (float32
-// with g: 2 lanes with 12-real links, 1 lane with 8-real links, 5 % ahead of
-// 2; float64: 1 lane, 3 % ahead of 2; 128 threads for all) and cache policy
-// (non-temporal for float32 in 8 reals, 1-4 % ahead of plain at one lane;
-// plain for float32 in 12 reals; non-temporal for float64); gf_pool_autotune
-// picks them for the resident mix.
+// block) and cache policy: for a pool full of large lattices (float32 with g:
+// 2 lanes, plain with 12-real links; 1 lane, non-temporal with 8-real links, 16
+// of 24^3x48 1256 us per sweep against 1289 at 2 lanes; float64: 1 lane,
+// non-temporal, 3051 us against 3153).  Small mixes want others: 8 lattices of
+// 12^4 to 16^3x32 in 8 reals 73 us, at 2 lanes 69; in float64 146, at 2 lanes
+// with plain accesses 116.  gf_pool_autotune picks for the resident mix.
 constexpr int kDefaultTps32 = 2, kDefaultTps32Min8 = 1, kDefaultTps64 = 1, kDefaultBlock = 128;
 // Staging buffer through which admissions and fetches move a job's canonical
 // links (18 doubles per link) in chunks; a multiple of one site's 4 links.
