@@ -413,6 +413,21 @@ __device__ __forceinline__ double delta_norm2(const M3<T>& K)
     return e0 * e0 + e1 * e1 + e2 * e2 + 2.0 * off;
 }
 
+// Keeps the compiler from mixing the instructions before and after.  It would
+// interleave the decodes (and encodes) of all links of a lane to hide their
+// latencies, at the price of their temporaries all living at once; other waves
+// hide them as well.  theta and F of 8 reals, whose threads do little else, then
+// need 122 registers in float32 instead of 237 and run 4 waves per SIMD instead of
+// 2 (float64 178 instead of 264, 2 instead of 1).  The sweeps keep their
+// number of waves; float64 ones and the heat bath still gain (24^3x48 float64 62.7
+// -> 60.6 us per half-sweep, the float32 heat bath of 32^4 72.3 -> 68.8), float32
+// overrelaxation does not (48^3x96 515 -> 522), so it goes without.
+template <bool ON = true>
+__device__ __forceinline__ void apart()
+{
+    if constexpr (ON) __builtin_amdgcn_sched_barrier(0);
+}
+
 // One site update of the site (parity, h) by lane r of its TPS-lane group.
 // TRACKG (float32 mixed-precision bulk): also g(x) <- G g(x) for the float32
 // gauge transformation accumulated since the original links; lane r of the
@@ -428,6 +443,7 @@ __device__ __forceinline__ double site_update(const F& f, const Geom& g, int par
                                               const Rule<R>& rule, const GField& gacc, bool est = false)
 {
     constexpr bool kMin8 = Min8Of<F>::value;
+    constexpr bool kApart = kMin8 && (sizeof(R) == 8 || MODE == HEATBATH);
     constexpr int NL = 8 / TPS;
     const Site s = decode_site(g, parity, h);
     const uint32_t lex = 2 * h + (uint32_t)(s.x & 1);
@@ -445,13 +461,17 @@ __device__ __forceinline__ double site_update(const F& f, const Geom& g, int par
     }
     if constexpr (kMin8) {
         static_assert(std::is_same<R, typename Min8Of<F>::R>::value, "decoded in the field's precision");
-        // every load first, then the decodes (each yields SU(3) to rounding)
+        // every load first, then the decodes (each yields SU(3) to rounding); see apart
         typename Min8Of<F>::C raw[NL][Min8Of<F>::N];
 #pragma unroll
         for (int k = 0; k < NL; ++k)
             load_min8_raw<nt_loads(CP)>(f, bwd[k] ? 1 - parity : parity, mu_of[k], at[k], raw[k]);
 #pragma unroll
-        for (int k = 0; k < NL; ++k) decode_min8(raw[k], U[k]);
+        for (int k = 0; k < NL; ++k) {
+            apart<kApart>();
+            decode_min8(raw[k], U[k]);
+        }
+        apart<kApart>();
     } else {
 #pragma unroll
         for (int k = 0; k < NL; ++k)
@@ -496,6 +516,7 @@ __device__ __forceinline__ double site_update(const F& f, const Geom& g, int par
 
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
+        apart<kApart>();
         if (bwd[k])
             right_mul_dag_rows01(G, U[k]);
         else
@@ -663,13 +684,11 @@ __device__ __forceinline__ void measure_site(const Field& f, const Geom& g, int 
             K.re[i][j] = 0.0;
             K.im[i][j] = 0.0;
         }
-#pragma unroll
-    for (int mu = 0; mu < NDIR; ++mu) {
-        M3<double> u;
-        load_full_f64(f, parity, mu, h, u);
+    auto forward = [&](const M3<double>& u) {
         fr += u.re[0][0] + u.re[1][1] + u.re[2][2];
         m_add(K, u);
-        load_full_f64(f, 1 - parity, mu, back_h(g, h, s, mu), u);
+    };
+    auto backward = [&](const M3<double>& u) {
 #pragma unroll
         for (int i = 0; i < 3; ++i)
 #pragma unroll
@@ -677,6 +696,32 @@ __device__ __forceinline__ void measure_site(const Field& f, const Geom& g, int 
                 K.re[i][j] += u.re[j][i];
                 K.im[i][j] -= u.im[j][i];
             }
+    };
+    M3<double> u;
+    if constexpr (Min8Of<Field>::value) {
+        typename Min8Of<Field>::C p[2 * NDIR][Min8Of<Field>::N];
+#pragma unroll
+        for (int mu = 0; mu < NDIR; ++mu) {
+            load_min8_raw(f, parity, mu, h, p[2 * mu]);
+            load_min8_raw(f, 1 - parity, mu, back_h(g, h, s, mu), p[2 * mu + 1]);
+        }
+#pragma unroll
+        for (int mu = 0; mu < NDIR; ++mu) {
+            apart();
+            decode_min8(p[2 * mu], u);
+            forward(u);
+            apart();
+            decode_min8(p[2 * mu + 1], u);
+            backward(u);
+        }
+    } else {
+#pragma unroll
+        for (int mu = 0; mu < NDIR; ++mu) {
+            load_full_f64(f, parity, mu, h, u);
+            forward(u);
+            load_full_f64(f, 1 - parity, mu, back_h(g, h, s, mu), u);
+            backward(u);
+        }
     }
     th = delta_norm2(K);
 }
