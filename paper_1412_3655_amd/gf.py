@@ -270,14 +270,14 @@ class _Record:
     """What the binding keeps of a live lattice: its hip stream handle (None = the default
     stream), so that the device-array calls can order that stream against torch's, with the
     torch stream and the two events they do it with (an event may be recorded again once the
-    wait on it is enqueued), and its canonical array's size.  A wait_stream per call, which makes
-    a stream object and an event each time, cost 25 us of host time in gf_set_links and 34 us in
-    gf_get_links, as much as the GPU needs for 10 half-sweeps of 8^4."""
+    wait on it is enqueued).  A wait_stream per call, which makes a stream object and an event
+    each time, cost 25 us of host time in gf_set_links and 34 us in gf_get_links, as much as
+    the GPU needs for 10 half-sweeps of 8^4."""
 
-    __slots__ = ("handle", "volume", "per_site", "device", "stream", "before", "after")
+    __slots__ = ("handle", "device", "stream", "before", "after")
 
-    def __init__(self, handle, volume, per_site):
-        self.handle, self.volume, self.per_site = handle, volume, per_site
+    def __init__(self, handle):
+        self.handle = handle
         self.device = self.stream = self.before = self.after = None
 
 
@@ -305,8 +305,7 @@ def gf_create_lattice(dims, prec: int = GF_FP64, stream=None, group: int = 3, st
                 err = GFError(st, lib().gf_last_error().decode(errors="replace"))
                 lib().gf_destroy_lattice(out)
                 raise err
-    nc = 2 if group == 2 else 3
-    _LATTICES[out.value] = _Record(h, d[0] * d[1] * d[2] * d[3], 8 * nc * nc)
+    _LATTICES[out.value] = _Record(h)
     return out
 
 
@@ -345,13 +344,7 @@ def gf_destroy_lattice(lat) -> None:
 def _record(lat) -> _Record:
     """The lattice's record (made for the call, on the default stream, for a handle that did not
     come from this module's gf_create_lattice)."""
-    key = getattr(lat, "value", lat)
-    r = _LATTICES.get(key)
-    if r is None:
-        volume, _ = gf_lattice_info(lat)
-        nc = gf_lattice_group(lat)
-        r = _Record(None, volume, 8 * nc * nc)
-    return r
+    return _LATTICES.get(getattr(lat, "value", lat)) or _Record(None)
 
 
 def _streams(r: _Record, tensor):
@@ -449,13 +442,16 @@ def gf_promote_fp64(lat) -> None:
 
 
 def gf_set_links(lat, links) -> None:
-    r = _record(lat)
+    volume, _ = gf_lattice_info(lat)
+    nc = gf_lattice_group(lat)
+    per_site = 4 * 2 * nc * nc
     if _is_device_tensor(links):
-        t = _device_links(links, r.volume, r.per_site)
+        r = _record(lat)
+        t = _device_links(links, volume, per_site)
         _before_lattice_reads(r, t)
         _call("gf_set_links_device", lat, t.data_ptr())
     else:
-        u = _host_links(links, r.volume, r.per_site)
+        u = _host_links(links, volume, per_site)
         _call("gf_set_links", lat, u.ctypes.data_as(_dp))
 
 
@@ -465,17 +461,19 @@ def gf_set_links_device(lat, dev_ptr: int) -> None:
 
 def gf_get_links(lat, out=None):
     """Links as a canonical array: into `out` (numpy or device tensor) or a new numpy array."""
-    r = _record(lat)
+    volume, _ = gf_lattice_info(lat)
+    nc = gf_lattice_group(lat)
+    per_site = 4 * 2 * nc * nc
     if out is None:
-        nc = 2 if r.per_site == 32 else 3
-        out = np.empty((r.volume, 4, nc, nc, 2), dtype=np.float64)
+        out = np.empty((volume, 4, nc, nc, 2), dtype=np.float64)
     if _is_device_tensor(out):
-        t = _device_links(out, r.volume, r.per_site)
+        r = _record(lat)
+        t = _device_links(out, volume, per_site)
         _before_lattice_reads(r, t)  # earlier torch work on `out` completes first
         _call("gf_get_links_device", lat, t.data_ptr())
         _after_lattice_writes(r, t)
     else:
-        u = _host_links(out, r.volume, r.per_site)
+        u = _host_links(out, volume, per_site)
         _call("gf_get_links", lat, u.ctypes.data_as(_dp))
     return out
 
