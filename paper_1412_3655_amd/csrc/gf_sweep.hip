@@ -35,7 +35,9 @@ bool sweep_config_valid(const SweepConfig& c)
 //     repeating the subgroup algebra in 4 (32^4 float32 8-real 99 against 126);
 //     one lane for the heat bath, which samples in every lane, unless the
 //     lattice leaves SIMDs idle (16^4 float32: 2 lanes 31, 1 lane 35; 32^4: 165
-//     at 1 lane, 194 at 2).
+//     at 1 lane, 194 at 2), in blocks of 64, which spread the few waves of a
+//     middling lattice evenly (16^3x32 float32 37 us, blocks of 128 45; 24^3x48
+//     8 reals 107, 113).
 SweepConfig default_sweep_config(const Geom& g, bool f64, int reals, bool heat_bath)
 {
     const uint64_t bytes = (uint64_t)g.vh * 8 * (uint64_t)reals * (f64 ? 8 : 4);
@@ -47,7 +49,7 @@ SweepConfig default_sweep_config(const Geom& g, bool f64, int reals, bool heat_b
     const bool nt = bytes <= (48u << 20);
     if (g.vh <= kTiny) return SweepConfig{reals == 8 || heat_bath ? 8 : 4, 64, 0, 0};
     if (g.vh <= kSmall) return SweepConfig{reals == 8 || heat_bath ? 4 : 2, 64, 1, 0};
-    if (heat_bath && g.vh > kMedium) return SweepConfig{1, f64 ? 64 : 128, nt ? 1 : 0, 0};
+    if (heat_bath && g.vh > kMedium) return SweepConfig{1, 64, nt ? 1 : 0, 0};
     if (nt) return SweepConfig{2, 256, 1, 0};
     return SweepConfig{2, reals == 8 ? 64 : 256, 0, 0};
 }
