@@ -428,6 +428,17 @@ __device__ __forceinline__ void apart()
     if constexpr (ON) __builtin_amdgcn_sched_barrier(0);
 }
 
+// Has the coefficients in scalar registers here: while the links are on their way,
+// neither before their addresses nor with a wait of its own at the first subgroup.
+__device__ __forceinline__ void fetch(const OrPower& w)
+{
+    static_assert(OrPower::N == 11, "all of them");
+    asm volatile("" ::"s"(w.p[0]), "s"(w.p[1]), "s"(w.p[2]), "s"(w.p[3]), "s"(w.p[4]), "s"(w.p[5]), "s"(w.p[6]),
+                 "s"(w.p[7]), "s"(w.p[8]), "s"(w.p[9]), "s"(w.p[10]), "s"(w.q[0]), "s"(w.q[1]), "s"(w.q[2]),
+                 "s"(w.q[3]), "s"(w.q[4]), "s"(w.q[5]), "s"(w.q[6]), "s"(w.q[7]), "s"(w.q[8]), "s"(w.q[9]),
+                 "s"(w.q[10]));
+}
+
 // One site update of the site (parity, h) by lane r of its TPS-lane group.
 // TRACKG (float32 mixed-precision bulk): also g(x) <- G g(x) for the float32
 // gauge transformation accumulated since the original links; lane r of the
@@ -476,6 +487,8 @@ __device__ __forceinline__ double site_update(const F& f, const Geom& g, int par
 #pragma unroll
         for (int k = 0; k < NL; ++k)
             load_rows01<nt_loads(CP)>(f, bwd[k] ? 1 - parity : parity, mu_of[k], at[k], U[k]);
+        apart();  // or arithmetic on the first links holds up the loads of the last
+        if constexpr (MODE == OR_EXACT && sizeof(R) == 8) fetch(rule.power);
         // Row 2 is rebuilt from the two stored rows, so a departure d from unitarity
         // of those rows becomes up to ~2d after an update that mixes the rows.  Every
         // heat-bath update mixes them strongly (d would grow ~1.35x per sweep), so the
