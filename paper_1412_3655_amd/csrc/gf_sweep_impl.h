@@ -31,7 +31,7 @@ __device__ __forceinline__ void half_sweep_body(const F& f, const Geom& g, int p
     // one another, each about a memory latency in the few waves of a small lattice
     // (with the loads of 12-real links all issued before the first use, and the
     // power's coefficients fetched behind them: 8^4 float64 to theta < 1e-12 in
-    // 290 sweeps 3470 -> 3280 us, 48^3x96 1548 -> 1526 us per half-sweep).
+    // 290 sweeps 3470 -> 3350 us, 48^3x96 1545 -> 1525 us per half-sweep).
     const uint32_t blocks = gridDim.x;
     asm volatile("" ::"s"(blocks), "s"(parity), "s"(f.base), "s"(f.ld), "s"(g.n[0]), "s"(g.n[1]), "s"(g.n[2]),
                  "s"(g.n[3]), "s"(g.hx), "s"(g.vh), "s"(g.hs1), "s"(g.hs2), "s"(g.hs3), "s"(g.div_hx.m),
