@@ -455,6 +455,13 @@ __device__ __forceinline__ double site_update(const F& f, const Geom& g, int par
 {
     constexpr bool kMin8 = Min8Of<F>::value;
     constexpr bool kApart = kMin8 && (sizeof(R) == 8 || MODE == HEATBATH);
+    // 12 reals: all loads before the arithmetic on the first links, which holds the
+    // last ones up otherwise (us per sweep without -> with, best block of each): float64
+    // at 2 lanes and more (8^4 9.9 -> 9.2, 24^4 79.8 -> 77.8; heat bath at 2 lanes, 32^4
+    // 7 %), and the float32 heat bath at one or two (32^4 156.7 -> 142.0).  Not at one
+    // lane in float64 (16^3x32 28.8 -> 29.5), nor in float32 sweeps (two lanes, all
+    // blocks and policies: 32^4 1.1 % and 48^3x96 1.0 % slower with it).
+    constexpr bool kLoadsFirst = MODE == HEATBATH ? TPS == 2 || (TPS == 1 && sizeof(R) == 4) : sizeof(R) == 8 && TPS >= 2;
     constexpr int NL = 8 / TPS;
     const Site s = decode_site(g, parity, h);
     const uint32_t lex = 2 * h + (uint32_t)(s.x & 1);
@@ -487,8 +494,8 @@ __device__ __forceinline__ double site_update(const F& f, const Geom& g, int par
 #pragma unroll
         for (int k = 0; k < NL; ++k)
             load_rows01<nt_loads(CP)>(f, bwd[k] ? 1 - parity : parity, mu_of[k], at[k], U[k]);
-        apart();  // or arithmetic on the first links holds up the loads of the last
-        if constexpr (MODE == OR_EXACT && sizeof(R) == 8) fetch(rule.power);
+        apart<kLoadsFirst>();
+        if constexpr (MODE == OR_EXACT && kLoadsFirst) fetch(rule.power);
         // Row 2 is rebuilt from the two stored rows, so a departure d from unitarity
         // of those rows becomes up to ~2d after an update that mixes the rows.  Every
         // heat-bath update mixes them strongly (d would grow ~1.35x per sweep), so the

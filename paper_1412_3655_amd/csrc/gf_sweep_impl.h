@@ -26,16 +26,19 @@ template <typename R, int TPS, int MODE, int BLOCK, bool TRACKG, int CP, int NDI
 __device__ __forceinline__ void half_sweep_body(const F& f, const Geom& g, int parity, const Rule<R>& rule,
                                                 const GField& gacc, double* est)
 {
-    // What the addresses of the links need, in scalar registers before anything
-    // else: fetched where it is first used it came in three rounds that waited for
-    // one another, each about a memory latency in the few waves of a small lattice
-    // (with the loads of 12-real links all issued before the first use, and the
-    // power's coefficients fetched behind them: 8^4 float64 to theta < 1e-12 in
-    // 290 sweeps 3470 -> 3350 us, 48^3x96 1545 -> 1525 us per half-sweep).
     const uint32_t blocks = gridDim.x;
-    asm volatile("" ::"s"(blocks), "s"(parity), "s"(f.base), "s"(f.ld), "s"(g.n[0]), "s"(g.n[1]), "s"(g.n[2]),
-                 "s"(g.n[3]), "s"(g.hx), "s"(g.vh), "s"(g.hs1), "s"(g.hs2), "s"(g.hs3), "s"(g.div_hx.m),
-                 "s"(g.div_hx.shift), "s"(g.div_ny.m), "s"(g.div_ny.shift), "s"(g.div_nz.m), "s"(g.div_nz.shift));
+    // What the addresses of the links need, in scalar registers before anything
+    // else: fetched where it is first used it comes in three rounds that wait for one
+    // another, each about a memory latency in the few waves of a small lattice.  It
+    // pays for the shapes that float64 links in 12 reals take there (8^4 at 4 lanes,
+    // non-temporal: 9.7 -> 9.2 us per sweep; 12^4 at 2: 14.3 -> 13.6) and for no
+    // others: 4 lanes of float32 were 2 % slower with it at 8^4, 8 lanes 4 %, of 8 reals as
+    // much, one lane and 8 of float64 1 %, and a heat bath 1 %.
+    if constexpr (sizeof(R) == 8 && !Min8Of<F>::value && MODE != HEATBATH && (TPS == 2 || TPS == 4))
+        asm volatile("" ::"s"(blocks), "s"(parity), "s"(f.base), "s"(f.ld), "s"(g.n[0]), "s"(g.n[1]), "s"(g.n[2]),
+                     "s"(g.n[3]), "s"(g.hx), "s"(g.vh), "s"(g.hs1), "s"(g.hs2), "s"(g.hs3), "s"(g.div_hx.m),
+                     "s"(g.div_hx.shift), "s"(g.div_ny.m), "s"(g.div_ny.shift), "s"(g.div_nz.m),
+                     "s"(g.div_nz.shift));
     // With cached loads the white half-sweep takes the blocks in reverse
     // order, so it starts on the links the black half-sweep touched last,
     // which are still in the Infinity Cache (a 32^4 float64 field is 402 MB
