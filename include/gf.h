@@ -205,8 +205,9 @@ gf_status gf_lattice_info(gf_lattice lat, int64_t* volume, int64_t* device_bytes
  * least 2 waves per SIMD, at most 256 registers per lane; 2 only with tps 1,
  * and it changes only float64 kernels, the paper's register-limit axis of
  * Sec. 5).  Every valid choice gives bitwise the same links.  Default:
- * chosen from the lattice's size, precision and storage (more lanes and small
- * blocks for few sites, non-temporal accesses while the links fit the L2s). */
+ * chosen from the lattice's size, precision and storage (more lanes for fewer
+ * sites; non-temporal accesses for links of up to 24 to 48 MiB but the
+ * smallest, and for float32 links in 8 reals beyond the Infinity Cache). */
 gf_status gf_set_sweep_config(gf_lattice lat, gf_prec kernel, int32_t tps, int32_t block, int32_t nontemporal,
                               int32_t min_waves);
 

@@ -184,10 +184,11 @@ const OrOmega& or_omega(gf_lattice L, double omega)
 void default_configs(gf_lattice L)
 {
     const int r64 = L->group == 2 ? 4 : (min8_64(L) ? 8 : 12), r32 = L->group == 2 ? 4 : (L->min8 ? 8 : 12);
-    if (!L->set64) L->cfg64 = gf::default_sweep_config(L->geom, true, r64, false);
-    if (!L->set32) L->cfg32 = gf::default_sweep_config(L->geom, false, r32, false);
-    if (!L->set_hb64) L->cfg_hb64 = gf::default_sweep_config(L->geom, true, r64, true);
-    if (!L->set_hb32) L->cfg_hb32 = gf::default_sweep_config(L->geom, false, r32, true);
+    const bool g = L->gacc.base != nullptr;
+    if (!L->set64) L->cfg64 = gf::default_sweep_config(L->geom, true, r64, false, false);
+    if (!L->set32) L->cfg32 = gf::default_sweep_config(L->geom, false, r32, false, g);
+    if (!L->set_hb64) L->cfg_hb64 = gf::default_sweep_config(L->geom, true, r64, true, false);
+    if (!L->set_hb32) L->cfg_hb32 = gf::default_sweep_config(L->geom, false, r32, true, g);
 }
 
 gf_status do_half_sweep(gf_lattice L, int parity, double omega, int mode)

@@ -26,8 +26,9 @@ struct SweepConfig {
 bool sweep_config_valid(const SweepConfig& c);
 
 // The configuration of a lattice that was neither tuned nor configured, from its
-// size, the bytes of its links and their reals per link (12 or 8, SU(2): 4).
-SweepConfig default_sweep_config(const Geom& g, bool f64, int reals, bool heat_bath);
+// size, the bytes of its links, their reals per link (12 or 8, SU(2): 4) and
+// whether its float32 sweeps track g.
+SweepConfig default_sweep_config(const Geom& g, bool f64, int reals, bool heat_bath, bool tracked);
 
 // Gauge of a lattice's functional: Landau (K over all 4 directions) or
 // Coulomb (K over x, y, z; one independent problem per timeslice).

@@ -18,40 +18,81 @@ bool sweep_config_valid(const SweepConfig& c)
 }
 
 // Every configuration gives the same links, so only time decides.  The lines are
-// where the tuner's tables over 4^4 .. 48^3x96 in every precision and storage
-// cross; the rule's choice is within 3 % of the best of each table on average
-// (4 lanes, 256 threads, plain accesses everywhere: 19 %).
-//   - Few sites: a half-sweep is one round of waves and costs its latency, so a
-//     site's work is spread over lanes and the blocks over compute units (8^4
-//     float64, us per sweep: 4 lanes in blocks of 64 9.8, of 256 11.9; 8-real
-//     links, whose decode dominates, 8 lanes 10.6, 4 lanes 11.4).
-//   - A field that fits the 8 L2s (32 MiB, somewhat more as reads leave no dirty
-//     lines): non-temporal.  With plain stores the half-sweep ends by flushing
-//     the dirty field from L2, where non-temporal ones are long written through:
-//     16^4 float32 24.8 -> 12.0, SU(2) 16^3x32 float64 27.6 -> 10.9.  Beyond, plain
-//     loads find part of the previous half-sweep in the Infinity Cache (24^4
-//     float64 82 plain, 102 non-temporal).
-//   - Otherwise 2 lanes: enough waves per SIMD to hide the loads without
-//     repeating the subgroup algebra in 4 (32^4 float32 8-real 99 against 126);
-//     one lane for the heat bath, which samples in every lane, unless the
-//     lattice leaves SIMDs idle (16^4 float32: 2 lanes 31, 1 lane 35; 32^4: 165
-//     at 1 lane, 194 at 2), in blocks of 64, which spread the few waves of a
-//     middling lattice evenly (16^3x32 float32 37 us, blocks of 128 45; 24^3x48
-//     8 reals 107, 113).
-SweepConfig default_sweep_config(const Geom& g, bool f64, int reals, bool heat_bath)
+// where tables of all configurations over 41 lattices from 4^4 to 48^3x96, in every
+// precision and storage and both gauges, cross; the rule's choice is within 1.5 %
+// of the best of a table on average and within 10 % at worst.  (Below in us per
+// sweep.)
+//   - One round: a half-sweep of few sites costs the latency of a wave, so a site
+//     goes to as many lanes as leave at most one wave on each of the 1024 SIMDs:
+//     kOneRound sites per colour at one lane, half of that at two.  8 reals and the
+//     heat bath, whose decode or sampling is long, follow this to 8 lanes (heat
+//     bath of float64 12 reals: 7200 sites at 8 lanes 34.0, at 4 35.4; 32768 at 2
+//     42, at 1 48; 40960 at 1 49, at 2 69).  Sweeps of 12 reals repeat their algebra in
+//     every lane and change earlier (float64, 5120 sites: 2 lanes 10.8, 4 lanes
+//     12.6), and just below one lane's round more waves hide what a single one
+//     cannot (46080 sites: float64 12 reals, 2 lanes 21, 1 23; 8 reals, 4 lanes
+//     24, 1 27; float32 12 reals, 2 lanes 16.4, 1 18.5; 8 reals 20.7 and 22.0).
+//   - A field that the 8 L2s hold: non-temporal.  With plain stores the half-sweep
+//     ends by flushing the dirty field from L2, where non-temporal ones are long
+//     written through: 16^4 float32 24 -> 13, SU(2) 16^3x32 float64 27.6 -> 10.9.
+//     Beyond, plain loads find part of the previous half-sweep in the Infinity
+//     Cache.  The tables cross at 48 MiB for float64 (58 MiB: 42 plain, 47
+//     non-temporal) and 8 reals, at 30 MiB for float32 in 12 reals (46 MiB: plain
+//     30.3, non-temporal at two lanes 37.6), at 24 for SU(2) (28 MiB: 20.1 and
+//     22.3; its heat bath at 32).  Half a MiB has no time to flush: plain (SU(2),
+//     864 sites: 6.3 and 7.0).
+//   - Beyond, 2 lanes hide the loads without repeating the algebra in 4, but one is
+//     enough in float32 12 reals (32^4 118, 2 lanes 120) and in the heat bath (32^4
+//     142 and 170), there in blocks of 64, which spread the waves evenly.
+//   - Float32 links in 8 reals that the 256 MB Infinity Cache no longer holds (with
+//     g, if tracked) are non-temporal again (32^3x64 mixed 216, plain 243), and at
+//     one lane when they are far beyond (48^3x96 984, 2 lanes plain 1067).  Without
+//     g, between the two, one lane with plain accesses is 3 to 6 % ahead.
+SweepConfig default_sweep_config(const Geom& g, bool f64, int reals, bool heat_bath, bool tracked)
 {
+    constexpr uint32_t kOneRound = 65536;
+    constexpr uint64_t MiB = 1u << 20;
     const uint64_t bytes = (uint64_t)g.vh * 8 * (uint64_t)reals * (f64 ? 8 : 4);
-    constexpr uint32_t kTiny = 5120, kSmall = 12288, kMedium = 40960;
+    const uint32_t n = g.vh;
     if (reals == 4) {
-        const bool nt = g.vh > kTiny && bytes <= (32u << 20);
-        return SweepConfig{1, g.vh <= kSmall ? 64 : 256, nt ? 1 : 0, 0};
+        if (bytes <= MiB / 2) return SweepConfig{1, 64, 0, 0};
+        if (bytes > (heat_bath ? 32 : 24) * MiB) return SweepConfig{1, 256, 0, 0};
+        if (n <= (heat_bath ? kOneRound / 2 : kOneRound / 8)) return SweepConfig{1, 64, 1, 0};
+        if (heat_bath) return SweepConfig{1, 256, 1, 0};
+        if (n <= kOneRound / 2) return SweepConfig{1, 128, 1, 0};
+        if (n <= kOneRound) return SweepConfig{1, 256, 1, 0};
+        if (f64) return SweepConfig{1, 128, 1, 0};
+        return SweepConfig{1, n <= 2 * kOneRound ? 512 : 256, 1, 0};
     }
-    const bool nt = bytes <= (48u << 20);
-    if (g.vh <= kTiny) return SweepConfig{reals == 8 || heat_bath ? 8 : 4, 64, 0, 0};
-    if (g.vh <= kSmall) return SweepConfig{reals == 8 || heat_bath ? 4 : 2, 64, 1, 0};
-    if (heat_bath && g.vh > kMedium) return SweepConfig{1, 64, nt ? 1 : 0, 0};
-    if (nt) return SweepConfig{2, 256, 1, 0};
-    return SweepConfig{2, reals == 8 ? 64 : 256, 0, 0};
+    const bool in_l2 = bytes <= 48 * MiB;
+    if (reals == 8 || heat_bath) {
+        if (n <= (heat_bath || !f64 ? kOneRound / 8 : 6144)) return SweepConfig{8, 64, 0, 0};
+        if (n <= kOneRound / 4) return SweepConfig{4, 256, 1, 0};
+        if (n <= kOneRound / 2) return SweepConfig{2, 256, 1, 0};
+        if (heat_bath) return SweepConfig{1, 64, in_l2 ? 1 : 0, 0};
+        if (f64) {
+            if (n <= kOneRound / 4 * 3) return SweepConfig{4, 64, 1, 0};
+            if (n <= kOneRound) return SweepConfig{1, 256, 1, 0};
+            return in_l2 ? SweepConfig{2, 256, 1, 0} : SweepConfig{2, 64, 0, 0};
+        }
+        // 1 lane up to two thirds of its round, and again towards the end of its second
+        if (n <= kOneRound / 3 * 2 || (n > kOneRound / 2 * 3 && n <= 2 * kOneRound)) return SweepConfig{1, 256, 1, 0};
+        const uint64_t all = bytes + (tracked ? (uint64_t)n * 2 * 48 : 0);
+        if (all > 352 * MiB) return SweepConfig{1, 64, 1, 0};
+        if (all > 256 * MiB) return tracked ? SweepConfig{2, 64, 1, 0} : SweepConfig{1, 64, 0, 0};
+        return SweepConfig{2, 64, in_l2 ? 1 : 0, 0};
+    }
+    if (n <= (f64 ? 2560 : kOneRound / 16)) return SweepConfig{4, 64, 0, 0};
+    if (n <= kOneRound / 8) return f64 ? SweepConfig{2, 64, 1, 0} : SweepConfig{4, 128, 1, 0};
+    if (n <= kOneRound / 4) return SweepConfig{2, 128, 1, 0};
+    if (n <= kOneRound / 2) return SweepConfig{2, 256, 1, 0};
+    if (f64) {
+        if (n <= kOneRound / 4 * 3) return SweepConfig{2, 64, 1, 0};
+        return n <= kOneRound ? SweepConfig{1, 64, 1, 0} : SweepConfig{2, 256, 0, 0};
+    }
+    if (n <= kOneRound / 3 * 2) return SweepConfig{1, 256, 1, 0};
+    if (n <= kOneRound / 8 * 7) return SweepConfig{2, 64, 1, 0};
+    return n <= kOneRound / 4 * 5 ? SweepConfig{2, 128, 1, 0} : SweepConfig{1, 256, 0, 0};
 }
 
 hipError_t launch_or_half_sweep(const LinkField<double>& f, const Geom& g, int parity, const OrOmega& om, int mode,
