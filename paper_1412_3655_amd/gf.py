@@ -366,14 +366,14 @@ def _streams(r: _Record, tensor):
 def _before_lattice_reads(r: _Record, tensor) -> None:
     """The lattice's stream waits for torch's current stream (which produced the
     tensor) unless that has nothing left to do (a wait between two queues holds the
-    GPU up for some 10 us; a capturing stream cannot be asked), and the caching
-    allocator keeps the tensor's memory until the lattice's stream has used it."""
-    import torch
-
+    GPU up for some 10 us), and the caching allocator keeps the tensor's memory until
+    the lattice's stream has used it.  Only the default stream is asked: it is never
+    captured, while the query of another fails if that stream is being captured, or
+    any stream is by another thread, and ends the capture."""
     pair = _streams(r, tensor)
     if pair is not None:
         cur, ls = pair
-        if torch.cuda.is_current_stream_capturing() or not cur.query():
+        if cur.cuda_stream or not cur.query():
             r.before.record(cur)
             ls.wait_event(r.before)
         tensor.record_stream(ls)
