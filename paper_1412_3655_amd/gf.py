@@ -14,6 +14,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import threading
 from dataclasses import dataclass
 
 import numpy as np
@@ -269,16 +270,17 @@ def gf_last_error() -> str:
 class _Record:
     """What the binding keeps of a live lattice: its hip stream handle (None = the default
     stream), so that the device-array calls can order that stream against torch's, with the
-    torch stream and the two events they do it with (an event may be recorded again once the
-    wait on it is enqueued).  A wait_stream per call, which makes a stream object and an event
-    each time, cost 25 us of host time in gf_set_links and 34 us in gf_get_links, as much as
-    the GPU needs for 10 half-sweeps of 8^4."""
+    torch stream and the event they do it with on each device (an event may be recorded again
+    once the wait on it is enqueued, so the two are done under the lock).  A wait_stream per
+    call, which makes a stream object and an event each time, cost 25 us of host time in
+    gf_set_links and 34 us in gf_get_links, as much as the GPU needs for 10 half-sweeps of 8^4."""
 
-    __slots__ = ("handle", "device", "stream", "before", "after")
+    __slots__ = ("handle", "lock", "streams")
 
     def __init__(self, handle):
         self.handle = handle
-        self.device = self.stream = self.before = self.after = None
+        self.lock = threading.Lock()
+        self.streams = {}  # device -> (stream, event)
 
 
 _LATTICES = {}
@@ -349,18 +351,25 @@ def _record(lat) -> _Record:
 
 def _streams(r: _Record, tensor):
     """(torch's current stream on the tensor's device, the lattice's stream as a torch
-    stream), or None when the two are the same stream."""
+    stream, an event of that device), or None when the two are the same stream."""
     import torch
 
     dev = tensor.device
     cur = torch.cuda.current_stream(dev)
     if (r.handle or 0) == int(cur.cuda_stream):
         return None
-    if r.device != dev:
-        r.device = dev
-        r.stream = torch.cuda.ExternalStream(r.handle, device=dev) if r.handle else torch.cuda.default_stream(dev)
-        r.before, r.after = torch.cuda.Event(), torch.cuda.Event()
-    return cur, r.stream
+    got = r.streams.get(dev)
+    if got is None:
+        ls = torch.cuda.ExternalStream(r.handle, device=dev) if r.handle else torch.cuda.default_stream(dev)
+        got = r.streams.setdefault(dev, (ls, torch.cuda.Event()))
+    return (cur, *got)
+
+
+def _order(r: _Record, event, first, then) -> None:
+    """Stream `then` waits for what stream `first` has been given."""
+    with r.lock:
+        event.record(first)
+        then.wait_event(event)
 
 
 def _before_lattice_reads(r: _Record, tensor) -> None:
@@ -370,23 +379,21 @@ def _before_lattice_reads(r: _Record, tensor) -> None:
     the lattice's stream has used it.  Only the default stream is asked: it is never
     captured, while the query of another fails if that stream is being captured, or
     any stream is by another thread, and ends the capture."""
-    pair = _streams(r, tensor)
-    if pair is not None:
-        cur, ls = pair
+    streams = _streams(r, tensor)
+    if streams is not None:
+        cur, ls, event = streams
         if cur.cuda_stream or not cur.query():
-            r.before.record(cur)
-            ls.wait_event(r.before)
+            _order(r, event, cur, ls)
         tensor.record_stream(ls)
 
 
 def _after_lattice_writes(r: _Record, tensor) -> None:
     """Torch's current stream waits for the lattice's stream (which wrote the tensor)."""
-    pair = _streams(r, tensor)
-    if pair is not None:
-        cur, ls = pair
+    streams = _streams(r, tensor)
+    if streams is not None:
+        cur, ls, event = streams
         tensor.record_stream(ls)
-        r.after.record(ls)
-        cur.wait_event(r.after)
+        _order(r, event, ls, cur)
 
 
 def gf_lattice_info(lat):

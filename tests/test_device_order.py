@@ -96,6 +96,33 @@ def test_idle_default_stream_is_not_waited_for(binding):
         assert ((LATTICE, "waits for", 0) in LOG) == (not idle)
 
 
+@pytest.mark.parametrize("call", [gf.gf_set_links, gf.gf_get_links])
+def test_threads_share_a_lattice(binding, call):
+    """Each thread's call comes behind what that thread's current stream was given, though the
+    threads take turns between any two steps."""
+    go = threading.Barrier(2)
+    failed = []
+
+    def thread(handle):
+        try:
+            binding(_Stream(handle))
+            go.wait()
+            call(LATTICE, _Tensor())
+        except Exception as e:  # noqa: BLE001
+            failed.append(e)
+
+    threads = [threading.Thread(target=thread, args=(h,)) for h in (0x2000, 0x3000)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed
+    before = [entry for entry in LOG if entry[:2] == (LATTICE, "waits for")]
+    assert sorted(of for _, _, of in before) == [0x2000, 0x3000]
+    if call is gf.gf_get_links:  # and each current stream behind the lattice's
+        assert {entry for entry in LOG if entry[0] != LATTICE} == {(h, "waits for", LATTICE) for h in (0x2000, 0x3000)}
+
+
 @pytest.mark.gpu
 def test_beside_another_threads_capture():
     """Links from and to device arrays, on a stream of torch's other than the default one, while
@@ -138,3 +165,29 @@ def test_beside_another_threads_capture():
     torch.cuda.synchronize()
     assert float(captured[0].sum()) == 128.0
     assert np.array_equal(out.cpu().numpy()[:, :, :2], u[:, :, :2])
+
+
+@pytest.mark.gpu
+def test_captured_with_torchs_work():
+    """Links taken by a graph that torch captures, from a lattice on a stream of its own: every
+    replay takes the present links, and eager calls in between use the same events."""
+    dims = (6, 4, 4, 6)
+    links = [torch.from_numpy(gi.gen_links(dims, 0.8, k)).cuda() for k in (34, 35, 36)]
+    out, twice, eager = (torch.empty_like(links[0]) for _ in range(3))
+    with gf.Lattice(dims, stream=torch.cuda.Stream()) as lat:
+        lat.set_links(links[0])
+        lat.get_links(out)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+            lat.get_links(out)
+            torch.mul(out, 2.0, out=twice)
+        for u in (*links, links[0]):
+            lat.set_links(u)
+            lat.sweep(1, 1.7)
+            lat.get_links(eager)
+            torch.cuda.synchronize()
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, eager) and torch.equal(twice, 2.0 * eager)
