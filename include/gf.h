@@ -265,11 +265,21 @@ gf_status gf_set_links(gf_lattice lat, const double* host);
 /* Same, from a device canonical array (hip device pointer).  Async. */
 gf_status gf_set_links_device(gf_lattice lat, const double* dev);
 
+/* Same, in the order of hip_stream (a stream of the lattice's device, NULL: the
+ * default one): after the work that hip_stream has been given, which may write
+ * the array, and before what it is given next, which may overwrite it.  What
+ * the lattice's stream is given next sees the new links.  Async; hip_stream may
+ * be being captured. */
+gf_status gf_set_links_device_on(gf_lattice lat, const double* dev, void* hip_stream);
+
 /* Download links into a host canonical array (row 2 rebuilt).  Syncs. */
 gf_status gf_get_links(gf_lattice lat, double* host);
 
 /* Same, into a device canonical array.  Async. */
 gf_status gf_get_links_device(gf_lattice lat, double* dev);
+
+/* Same, in the order of hip_stream, as gf_set_links_device_on. */
+gf_status gf_get_links_device_on(gf_lattice lat, double* dev, void* hip_stream);
 
 /* n_sweeps overrelaxation sweeps: each sweep updates every black site
  * ((x+y+z+t) even), then every white site.  A site update forms

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <map>
+#include <mutex>
 #include <string>
 #include <tuple>
 
@@ -17,6 +18,7 @@ struct gf_lattice_ {
     int32_t dims[4] = {0, 0, 0, 0};
     gf_prec prec = GF_FP64;
     hipStream_t stream = nullptr;
+    int device = 0;  // the device that was current when the lattice was made
     gf::Geom geom{};
     int64_t volume = 0;
     int64_t bytes = 0;
@@ -52,6 +54,8 @@ struct gf_lattice_ {
     // and g tracking plus 4 x gauge, tps, block, cache policy); only on a
     // non-default stream
     std::map<std::tuple<int32_t, double, int, int, int, int, int>, hipGraphExec_t> sweep_graphs;
+    hipEvent_t order = nullptr;  // orders another stream against this one (created on use)
+    std::mutex order_mutex;      // ... recorded and waited for in one step
 };
 
 namespace gf {

@@ -14,7 +14,6 @@ from __future__ import annotations
 
 import ctypes
 import os
-import threading
 from dataclasses import dataclass
 
 import numpy as np
@@ -138,8 +137,10 @@ _SIGNATURES = {
                     ctypes.POINTER(_i32), ctypes.POINTER(gf_tune_entry)],
     "gf_set_links": [_vp, _dp],
     "gf_set_links_device": [_vp, _vp],
+    "gf_set_links_device_on": [_vp, _vp, _vp],
     "gf_get_links": [_vp, _dp],
     "gf_get_links_device": [_vp, _vp],
+    "gf_get_links_device_on": [_vp, _vp, _vp],
     "gf_sweep_or": [_vp, _i32, ctypes.c_double, ctypes.c_int],
     "gf_half_sweep_or": [_vp, _i32, ctypes.c_double, ctypes.c_int],
     "gf_anneal": [_vp, _i32, ctypes.c_double, ctypes.c_double, ctypes.c_uint64],
@@ -267,25 +268,6 @@ def gf_last_error() -> str:
     return lib().gf_last_error().decode(errors="replace")
 
 
-class _Record:
-    """What the binding keeps of a live lattice: its hip stream handle (None = the default
-    stream), so that the device-array calls can order that stream against torch's, with the
-    torch stream and the event they do it with on each device (an event may be recorded again
-    once the wait on it is enqueued, so the two are done under the lock).  A wait_stream per
-    call, which makes a stream object and an event each time, cost 25 us of host time in
-    gf_set_links and 34 us in gf_get_links, as much as the GPU needs for 10 half-sweeps of 8^4."""
-
-    __slots__ = ("handle", "lock", "streams")
-
-    def __init__(self, handle):
-        self.handle = handle
-        self.lock = threading.Lock()
-        self.streams = {}  # device -> (stream, event)
-
-
-_LATTICES = {}
-
-
 def gf_create_lattice(dims, prec: int = GF_FP64, stream=None, group: int = 3, storage: int = 12) -> ctypes.c_void_p:
     """group 3: SU(3) (gf_create_lattice); group 2: SU(2) (gf_create_lattice_su2).
     storage 8: SU(3) links of the sweeping precision in 8 reals (GF_FP64: gf_create_lattice_min8;
@@ -307,7 +289,6 @@ def gf_create_lattice(dims, prec: int = GF_FP64, stream=None, group: int = 3, st
                 err = GFError(st, lib().gf_last_error().decode(errors="replace"))
                 lib().gf_destroy_lattice(out)
                 raise err
-    _LATTICES[out.value] = _Record(h)
     return out
 
 
@@ -340,60 +321,6 @@ def gf_lattice_group(lat) -> int:
 
 def gf_destroy_lattice(lat) -> None:
     _call("gf_destroy_lattice", lat)
-    _LATTICES.pop(getattr(lat, "value", lat), None)
-
-
-def _record(lat) -> _Record:
-    """The lattice's record (made for the call, on the default stream, for a handle that did not
-    come from this module's gf_create_lattice)."""
-    return _LATTICES.get(getattr(lat, "value", lat)) or _Record(None)
-
-
-def _streams(r: _Record, tensor):
-    """(torch's current stream on the tensor's device, the lattice's stream as a torch
-    stream, an event of that device), or None when the two are the same stream."""
-    import torch
-
-    dev = tensor.device
-    cur = torch.cuda.current_stream(dev)
-    if (r.handle or 0) == int(cur.cuda_stream):
-        return None
-    got = r.streams.get(dev)
-    if got is None:
-        ls = torch.cuda.ExternalStream(r.handle, device=dev) if r.handle else torch.cuda.default_stream(dev)
-        got = r.streams.setdefault(dev, (ls, torch.cuda.Event()))
-    return (cur, *got)
-
-
-def _order(r: _Record, event, first, then) -> None:
-    """Stream `then` waits for what stream `first` has been given."""
-    with r.lock:
-        event.record(first)
-        then.wait_event(event)
-
-
-def _before_lattice_reads(r: _Record, tensor) -> None:
-    """The lattice's stream waits for torch's current stream (which produced the
-    tensor) unless that has nothing left to do (a wait between two queues holds the
-    GPU up for some 10 us), and the caching allocator keeps the tensor's memory until
-    the lattice's stream has used it.  Only the default stream is asked: it is never
-    captured, while the query of another fails if that stream is being captured, or
-    any stream is by another thread, and ends the capture."""
-    streams = _streams(r, tensor)
-    if streams is not None:
-        cur, ls, event = streams
-        if cur.cuda_stream or not cur.query():
-            _order(r, event, cur, ls)
-        tensor.record_stream(ls)
-
-
-def _after_lattice_writes(r: _Record, tensor) -> None:
-    """Torch's current stream waits for the lattice's stream (which wrote the tensor)."""
-    streams = _streams(r, tensor)
-    if streams is not None:
-        cur, ls, event = streams
-        tensor.record_stream(ls)
-        _order(r, event, ls, cur)
 
 
 def gf_lattice_info(lat):
@@ -448,15 +375,24 @@ def gf_promote_fp64(lat) -> None:
     _call("gf_promote_fp64", lat)
 
 
+def _current_stream(tensor):
+    """Handle of torch's current stream on the tensor's device (None = the default stream), which
+    the caching allocator holds the tensor's memory for."""
+    import torch
+
+    cur = torch.cuda.current_stream(tensor.device)
+    tensor.record_stream(cur)
+    return cur.cuda_stream or None
+
+
 def gf_set_links(lat, links) -> None:
+    """From a canonical array: numpy, or a device tensor in the order of torch's current stream."""
     volume, _ = gf_lattice_info(lat)
     nc = gf_lattice_group(lat)
     per_site = 4 * 2 * nc * nc
     if _is_device_tensor(links):
-        r = _record(lat)
         t = _device_links(links, volume, per_site)
-        _before_lattice_reads(r, t)
-        _call("gf_set_links_device", lat, t.data_ptr())
+        _call("gf_set_links_device_on", lat, t.data_ptr(), _current_stream(t))
     else:
         u = _host_links(links, volume, per_site)
         _call("gf_set_links", lat, u.ctypes.data_as(_dp))
@@ -467,18 +403,16 @@ def gf_set_links_device(lat, dev_ptr: int) -> None:
 
 
 def gf_get_links(lat, out=None):
-    """Links as a canonical array: into `out` (numpy or device tensor) or a new numpy array."""
+    """Links as a canonical array: into `out` (numpy, or a device tensor in the order of torch's
+    current stream) or a new numpy array."""
     volume, _ = gf_lattice_info(lat)
     nc = gf_lattice_group(lat)
     per_site = 4 * 2 * nc * nc
     if out is None:
         out = np.empty((volume, 4, nc, nc, 2), dtype=np.float64)
     if _is_device_tensor(out):
-        r = _record(lat)
         t = _device_links(out, volume, per_site)
-        _before_lattice_reads(r, t)  # earlier torch work on `out` completes first
-        _call("gf_get_links_device", lat, t.data_ptr())
-        _after_lattice_writes(r, t)
+        _call("gf_get_links_device_on", lat, t.data_ptr(), _current_stream(t))
     else:
         u = _host_links(out, volume, per_site)
         _call("gf_get_links", lat, u.ctypes.data_as(_dp))
@@ -487,6 +421,14 @@ def gf_get_links(lat, out=None):
 
 def gf_get_links_device(lat, dev_ptr: int) -> None:
     _call("gf_get_links_device", lat, int(dev_ptr))
+
+
+def gf_set_links_device_on(lat, dev_ptr: int, stream=None) -> None:
+    _call("gf_set_links_device_on", lat, int(dev_ptr), _stream_handle(stream))
+
+
+def gf_get_links_device_on(lat, dev_ptr: int, stream=None) -> None:
+    _call("gf_get_links_device_on", lat, int(dev_ptr), _stream_handle(stream))
 
 
 def gf_sweep_or(lat, n_sweeps: int, omega: float, mode: int = GF_OR_EXACT) -> None:
