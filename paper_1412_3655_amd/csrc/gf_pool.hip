@@ -258,7 +258,8 @@ __global__ void __launch_bounds__(PBLOCK) k_pool_reunit(const SlotDev* __restric
 
 // Tile b of a slot = measurement block (parity = b & 1, block = b >> 1) of the
 // single-lattice measurement, writing the same partial.  Each XCD takes a
-// contiguous run of the tiles, as there (block b runs on XCD b % 8).
+// contiguous run of the tiles, as there (block b runs on XCD b % 8): gridDim.x is a
+// multiple of kXcds, else tiles would be left out or done twice.
 template <typename R, bool M8>
 __global__ void __launch_bounds__(PBLOCK) k_pool_measure(const SlotDev* __restrict__ slots,
                                                          const Entry* __restrict__ list,
@@ -1018,7 +1019,8 @@ gf_status gf_pool_create(const gf_pool_config* cfg, void* hip_stream, gf_pool* o
         return fail(GF_E_HIP, "pool allocation failed: %s", hipGetErrorString(e));
     }
     // persistent grid of the reunitarisation / measurement kernels: a few resident blocks per compute unit
-    P->grid_other = 4 * (ncu + 7) / 8 * 8;  // whole rounds over the XCDs (k_pool_measure)
+    const int xcds = (int)kXcds;
+    P->grid_other = 4 * ((ncu + xcds - 1) / xcds * xcds);  // whole rounds over the XCDs (k_pool_measure)
     P->seg_tiles.assign(nseg, 0);
     std::memset(P->slots_pin, 0, sizeof(SlotDev) * c.max_slots);
     *out = P;
