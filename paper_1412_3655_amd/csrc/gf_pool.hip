@@ -57,8 +57,10 @@ constexpr int kHeatBathBlock = 128;  // threads per block of the heat-bath sweep
 // with plain accesses 116.  gf_pool_autotune picks for the resident mix.
 constexpr int kDefaultTps32 = 2, kDefaultTps32Min8 = 1, kDefaultTps64 = 1, kDefaultBlock = 128;
 // Staging buffer through which admissions and fetches move a job's canonical
-// links (18 doubles per link) in chunks; a multiple of one site's 4 links.
-constexpr size_t kStageLinks = (size_t)4 * 58254;  // 33.6 MB
+// links (18 doubles per link) in chunks of whole pairs of sites, 8 links each
+// (launch_pack_range refuses others).
+constexpr size_t kStageLinks = (size_t)8 * 29127;  // 33.6 MB
+static_assert(kStageLinks % 8 == 0, "whole pairs of sites");
 
 struct SlotDev {
     LinkField<double> f64;
