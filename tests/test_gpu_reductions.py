@@ -73,3 +73,17 @@ def test_su2(dims):
     tol = 8 * 2.0**-53 * np.sqrt(gi.volume(dims)) + 1e-15
     assert abs(got_th - th) <= 8 * tol * th
     assert abs(got_F - F) <= tol and abs(got_P - P) <= tol
+
+
+@pytest.mark.parametrize("group", [3, 2])
+@pytest.mark.parametrize("dims", [(4, 6, 2, 10), (14, 10, 10, 6), (24, 24, 24, 2), (2, 2, 2, 38)])
+def test_every_slice(dims, group):
+    """Timeslice by timeslice: a block's tile and timeslice come out of one number."""
+    u = (gi.gen_links if group == 3 else gi.gen_links_su2)(dims, 0.7, 4)
+    with gf.Lattice(dims, gauge=gf.GF_COULOMB, group=group) as lat:
+        lat.set_links(u)
+        th, F = lat.measure_timeslices()
+    want_th, want_F = (oracle.coulomb_measure if group == 3 else oracle.su2lat_coulomb_measure)(u, dims)[:2]
+    tol = 8 * 2.0**-53 * np.sqrt(gi.volume(dims) / dims[3]) + 1e-15
+    assert np.all(np.abs(np.asarray(th) - want_th) <= 8 * tol * np.asarray(want_th))
+    assert np.all(np.abs(np.asarray(F) - want_F) <= tol)
