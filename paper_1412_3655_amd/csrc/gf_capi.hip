@@ -175,9 +175,15 @@ void apply_config(gf_lattice L, gf_prec kernel, bool heat_bath, const SweepConfi
     }
 }
 
-const OrOmega& or_omega(gf_lattice L, double omega)
+const OrOmega& or_omega(gf_lattice L, double omega, bool power)
 {
-    if (L->om.omega != omega) L->om = make_or_omega(omega);
+    if (L->om.omega != omega || (power && !L->om_power)) {
+        L->om_power = power;
+        if (power)
+            L->om = make_or_omega(omega);
+        else
+            L->om.omega = omega;
+    }
     return L->om;
 }
 
@@ -193,7 +199,7 @@ void default_configs(gf_lattice L)
 
 gf_status do_half_sweep(gf_lattice L, int parity, double omega, int mode)
 {
-    const OrOmega& om = or_omega(L, omega);
+    const OrOmega& om = or_omega(L, omega, mode == GF_OR_EXACT && !is_fp32(L));
     if (L->group == 2) {
         if (is_fp32(L))
             GF_HIP(gf::launch_su2_or(su2_32(L), L->geom, parity, om, mode, L->cfg32, L->stream, L->gauge,
@@ -377,7 +383,7 @@ gf_status do_measure(gf_lattice L, double* theta, double* F)
 gf_status do_est_sweep(gf_lattice L, double omega, int mode, double* theta_est)
 {
     const SweepConfig& c = is_fp32(L) ? L->cfg32 : L->cfg64;
-    const OrOmega& om = or_omega(L, omega);
+    const OrOmega& om = or_omega(L, omega, mode == GF_OR_EXACT && !is_fp32(L));
     const bool su2 = L->group == 2;
     const uint32_t nb = su2 ? gf::su2_sweep_blocks(L->geom, c) : gf::sweep_blocks(L->geom, c);
     const size_t need = 4 * (size_t)nb;

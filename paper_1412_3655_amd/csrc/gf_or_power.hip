@@ -13,19 +13,32 @@ constexpr long double kPi = 3.14159265358979323846264338327950288L;
 // P(y) = (1 - T_omega(1 - y)) / y and Q(y) = U_{omega-1}(1 - y) from their
 // hypergeometric series 2F1(-omega, omega; 1/2; y/2) and omega 2F1(1 - omega,
 // 1 + omega; 3/2; y/2), whose terms fall by y/2 <= 0.15 each.
-void or_series(long double w, long double y, long double* P, long double* Q)
-{
-    long double c = 1.0L, p = 0.0L, d = w, q = w, yk = 1.0L;
-    for (int k = 1; k <= 32; ++k) {
-        c *= ((long double)(k - 1) * (k - 1) - w * w) / ((2 * k - 1) * (long double)k);
-        d *= ((long double)k * k - w * w) / ((2 * k + 1) * (long double)k);
-        p -= c * yk;
-        yk *= y;
-        q += d * yk;
+constexpr int kTerms = 32;
+
+struct OrSeries {
+    long double c[kTerms], d[kTerms], w;
+
+    explicit OrSeries(long double omega) : w(omega)
+    {
+        long double ck = 1.0L, dk = w;
+        for (int k = 1; k <= kTerms; ++k) {
+            c[k - 1] = ck *= ((long double)(k - 1) * (k - 1) - w * w) / ((2 * k - 1) * (long double)k);
+            d[k - 1] = dk *= ((long double)k * k - w * w) / ((2 * k + 1) * (long double)k);
+        }
     }
-    *P = p;
-    *Q = q;
-}
+
+    void sum(long double y, long double* P, long double* Q) const
+    {
+        long double p = 0.0L, q = w, yk = 1.0L;
+        for (int k = 0; k < kTerms; ++k) {
+            p -= c[k] * yk;
+            yk *= y;
+            q += d[k] * yk;
+        }
+        *P = p;
+        *Q = q;
+    }
+};
 
 // Monomial coefficients of the interpolant through (x_i, f_i), i < N (f is
 // overwritten by the divided differences).
@@ -41,17 +54,28 @@ void interpolate(const long double (&x)[N], long double (&f)[N], long double (&m
     }
 }
 
+// Chebyshev nodes of [0, 1 - 1/sqrt 2], y at psi = pi/4.
+struct Nodes {
+    long double x[OrPower::N];
+
+    Nodes()
+    {
+        constexpr int N = OrPower::N;
+        const long double top = 1.0L - sqrtl(0.5L);
+        for (int i = 0; i < N; ++i)
+            x[i] = 0.5L * top * (1.0L + cosl(kPi * (2 * i + 1) / (2 * N)));
+    }
+};
+
 void make_power(long double w, OrPower* out)
 {
     constexpr int N = OrPower::N;
-    const long double top = 1.0L - sqrtl(0.5L);  // y at psi = pi/4
-    long double x[N], fp[N], fq[N], p[N], q[N];
-    for (int i = 0; i < N; ++i) {
-        x[i] = 0.5L * top * (1.0L + cosl(kPi * (2 * i + 1) / (2 * N)));
-        or_series(w, x[i], &fp[i], &fq[i]);
-    }
-    interpolate<N>(x, fp, p);
-    interpolate<N>(x, fq, q);
+    static const Nodes nodes;
+    const OrSeries series(w);
+    long double fp[N], fq[N], p[N], q[N];
+    for (int i = 0; i < N; ++i) series.sum(nodes.x[i], &fp[i], &fq[i]);
+    interpolate<N>(nodes.x, fp, p);
+    interpolate<N>(nodes.x, fq, q);
     for (int k = 0; k < N; ++k) {
         out->p[k] = (double)p[k];
         out->q[k] = (double)q[k];

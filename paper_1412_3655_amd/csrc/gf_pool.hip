@@ -676,7 +676,7 @@ void fill_slot(gf_pool P, int slot)
     d.f32 = LinkField<float>{L->f32, L->geom.ld};
     d.gacc = L->gacc;
     d.g = L->geom;
-    const OrOmega& om = or_omega(L, j.p.omega);
+    const OrOmega& om = or_omega(L, j.p.omega, P->cfg.mode == GF_OR_EXACT);
     d.omega = om.omega;
     d.power = om.power;
     d.T0 = j.T0;
