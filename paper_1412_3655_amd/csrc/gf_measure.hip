@@ -148,8 +148,9 @@ __device__ __forceinline__ uint32_t column_tile(uint32_t q, uint32_t T, uint32_t
 // they load 19 links, hide them better.  The links at x + t^ are a timeslice
 // away, more than an XCD's L2 holds on a large lattice, so tiles go in columns
 // whose timeslice is about half an L2.  float64, 12 reals: 32^4 141 -> 122 us by
-// the halves, -> 118 by the columns (every link once at the rate of a large copy:
-// 80); 48^3x96 1501 -> 1412 -> 1236; float32 920 -> 884 -> 832; 8^4 7.4 -> 5.7.
+// the halves, -> 118 by the columns, called again and again (behind an upload 129;
+// every link once at the rate of a large copy: 62); 48^3x96 1501 -> 1412 -> 1236;
+// float32 920 -> 884 -> 832; 8^4 7.4 -> 5.7.
 // partial holds, per tile, the sums of colour 0 and colour 1.
 template <typename Field>
 __global__ void __launch_bounds__(RBLOCK) k_plaquette_halves(Field f, Geom g, uint32_t row, uint32_t col,

@@ -121,8 +121,9 @@ __device__ __forceinline__ constexpr R tan_clamp()
 // the reciprocal square root are good to 2^-24.4 and 2^-24.2, so one third-order
 // step ends at half a unit in the last place (square root: 0.6 before the
 // correction); the float32 seeds are good to 2^-23.3, and the residual
-// correction alone rounds the square root correctly (a refinement step before it
-// gave the same bits over 2e6 values).  The sweeps of 8-real links are bound by
+// correction alone rounds the square root of every float in [1/4, 2] correctly.
+// (With a refinement step before it, 6 of the 25 million reciprocal roots there
+// end one unit elsewhere, no nearer on the whole.)  The sweeps of 8-real links are bound by
 // their vector instructions: with these steps, an integer flag and picks of named
 // values on two masks a float32 wave at one lane per site went from 3966 to 3614
 // of them, a float64 one at two lanes from 2702 to 2466 (32^4 float32 at 4 lanes

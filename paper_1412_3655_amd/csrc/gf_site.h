@@ -79,7 +79,7 @@ constexpr double kTinySquare = 0x1p-960;
 // lanes per site issues 811 vector instructions instead of about 1400; the 8^4
 // sweep, which a chain of dependent operations bounds, went from 11.8 to 10.0
 // us, 16^4 from 20.0 to 17.7.  The error against values of higher precision is
-// smaller at every angle (rms, in 2^-53: 0.3 and 0.3 near the maximum, 1.2 and
+// no larger at any angle (rms, in 2^-53: 0.3 and 0.3 near the maximum, 1.2 and
 // 1.3 over random blocks; atan2 and sincos second).
 __device__ __forceinline__ Quat<double> or_power(const Quat<double>& a, const OrPower& w)
 {
@@ -148,9 +148,10 @@ __device__ __forceinline__ Quat<double> or_power(const Quat<double>& a, const Or
 
 // The same through the device library's float32 functions.  (The polynomials
 // would save a float32 sweep of 8-real links about 10 % of its instructions, but
-// any other rounding of b moves float32 results by their own error, which rough
-// inputs amplify up to 1e-3 at single sites within ten sweeps; float32 runs stay
-// reproducible instead.)
+// they round most elements otherwise, and float32 results would move by their own
+// error, which rough inputs amplify up to 1e-3 at single sites within ten sweeps.
+// The bits of float32 results are not promised from build to build, but so broad
+// a change is not made for that gain.)
 __device__ __forceinline__ Quat<float> or_power(const Quat<float>& a, float omega)
 {
     Quat<float> b;
@@ -420,8 +421,9 @@ __device__ __forceinline__ double delta_norm2(const M3<T>& K)
 // need 122 registers in float32 instead of 237 and run 4 waves per SIMD instead of
 // 2 (float64 178 instead of 264, 2 instead of 1).  The sweeps keep their
 // number of waves; float64 ones and the heat bath still gain (24^3x48 float64 62.7
-// -> 60.6 us per half-sweep, the float32 heat bath of 32^4 72.3 -> 68.8), float32
-// overrelaxation does not (48^3x96 515 -> 522), so it goes without.
+// -> 60.6 us per half-sweep, the float32 heat bath of 32^4 at T = 1 72.3 -> 68.8;
+// where it starts hotter, 84 to 87), float32 overrelaxation does not (48^3x96 515
+// -> 522), so it goes without.
 template <bool ON = true>
 __device__ __forceinline__ void apart()
 {
@@ -612,7 +614,7 @@ __device__ __forceinline__ double wave_sum(double v)
 // tile for x and mostly y, a few tiles on for z) finds it in that L2: logical
 // block xcd_block(b, n) for the block b of n, a permutation of 0..n-1.  theta
 // and F of 32^4 float64 113 -> 97 us (the links once at the rate of a large
-// copy: 80 us), of 48^3x96 1212 -> 825, of SU(2) 32^3x64 80 -> 46; plaquette of
+// copy: 62 us), of 48^3x96 1212 -> 825, of SU(2) 32^3x64 80 -> 46; plaquette of
 // 32^4 212 -> 172.  The partial sums keep their places, so theta and F are the
 // same bits.
 constexpr uint32_t kXcds = 8;
