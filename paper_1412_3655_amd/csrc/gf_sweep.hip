@@ -19,9 +19,8 @@ bool sweep_config_valid(const SweepConfig& c)
 
 // Every configuration gives the same links, so only time decides.  The lines are
 // where tables of all configurations over 41 lattices from 4^4 to 48^3x96, in every
-// precision and storage and both gauges, cross; the rule's choice is within 1.5 %
-// of the best of a table on average and within 10 % at worst.  (Below in us per
-// sweep.)
+// precision and storage and both gauges, cross; the rule's choice is within 2 % of
+// the best of a table on average and within 11 % at worst.  (Below in us per sweep.)
 //   - One round: a half-sweep of few sites costs the latency of a wave, so a site
 //     goes to as many lanes as leave at most one wave on each of the 1024 SIMDs:
 //     kOneRound sites per colour at one lane, half of that at two.  8 reals and the
