@@ -77,14 +77,15 @@ def _us(lat, anneal):
 ])
 def test_default_is_near_the_best(dims, prec, anneal, better):
     st = torch.cuda.Stream()
-    with torch.cuda.stream(st):
+    with torch.cuda.stream(st), gf.Lattice(dims, prec, stream=st) as lat, gf.Lattice(dims, prec, stream=st) as other:
         u = _links(dims, 3)
-        with gf.Lattice(dims, prec, stream=st) as lat:
-            lat.set_links(u)
-            default = _us(lat, anneal)
-            best = np.inf
+        lat.set_links(u)
+        other.set_links(u)
+        set_config = other.set_anneal_config if anneal else other.set_sweep_config
+        default = best = np.inf
+        for _ in range(3):  # in turn, so that a slow moment is no configuration's alone
+            default = min(default, _us(lat, anneal))
             for tps, block, nt in better:
-                set_config = lat.set_anneal_config if anneal else lat.set_sweep_config
                 set_config(tps, block, nontemporal=nt)
-                best = min(best, _us(lat, anneal))
+                best = min(best, _us(other, anneal))
     assert default <= 1.12 * best
